@@ -12,6 +12,7 @@
 #pragma once
 
 #include "binning.hpp"
+#include "small.hpp"
 #include "sph.hpp"
 
 namespace tfsph {
@@ -25,32 +26,8 @@ struct Inst {
     Phase<R> Pg, Pd;     // caller arrays of this instance (slices of the packed state)
     Sorted<R> Sg, Sd;    // workspace slices
     CellSolve<R> *cs;    // [ncell] per-cell solve
+    int mask_rows;       // neighbour mask words per gas particle in LDS (2D)
 };
-
-// exclusive scan of one int per thread for any blockDim.x <= 1024 (wave64)
-__device__ __forceinline__ int block_scan_any(int v, int *lds_waves, int &total)
-{
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-    const int nwaves = (blockDim.x + 63) >> 6;
-    int x = v;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const int y = __shfl_up(x, off, 64);
-        if (lane >= off) x += y;
-    }
-    if (lane == 63) lds_waves[wave] = x;
-    __syncthreads();
-    int pre = 0;
-    total = 0;
-    for (int w = 0; w < nwaves; ++w) {
-        const int t = lds_waves[w];
-        if (w < wave) pre += t;
-        total += t;
-    }
-    __syncthreads();
-    return pre + x - v;
-}
 
 // start[c] = sum of count[0..c), start[ncell] = total, for one instance: each
 // thread sums a contiguous run of cells, one block scan combines the runs.
@@ -92,7 +69,7 @@ __device__ __forceinline__ void block_scan_cells(const int *count, int *start, i
 // counting sort are claimed while the particles are finished (the new cell is
 // known there); `first` does the counting from scratch for the first step of
 // a launch, since the state may have been written outside this kernel.
-template <typename R, int DIM>
+template <typename R, int DIM, int KIND>
 __device__ __forceinline__ void batched_step(const Inst<R> &I, int *lds, unsigned int *flags, int &bad, int &one,
                                              R &s2, bool first)
 {
@@ -145,7 +122,7 @@ __device__ __forceinline__ void batched_step(const Inst<R> &I, int *lds, unsigne
     __syncthreads();
     for (int a = tid; a < ng; a += nt) density_store<R, DIM>(G, I.Ph, I.Sg, a, 1);
     __syncthreads();
-    for (int a = tid; a < ng; a += nt) gas_predict<R, DIM>(G, I.Ph, I.Sg, I.Pg, a);
+    for (int a = tid; a < ng; a += nt) gas_predict<R, DIM, KIND>(G, I.Ph, I.Sg, I.Pg, a);
     __syncthreads();
     for (int c = tid; c < ncell; c += nt) one += solve_cell<R, DIM>(I.Ph, I.Sg, I.Sd, c, I.cs[c]) ? 1 : 0;
     __syncthreads();
@@ -170,18 +147,34 @@ __device__ __forceinline__ void batched_step(const Inst<R> &I, int *lds, unsigne
     __syncthreads();
 }
 
-// grid = number of instances; block b advances instance order[b] by n_steps
-template <typename R, int DIM>
+// grid = number of instances; block b advances instance order[b] by n_steps.  An
+// instance whose working set fits lds_bytes of dynamic LDS runs there
+// (small_steps()); the others work in global memory.  KIND: the force-loop kind
+// every instance shares, or -1.
+template <typename R, int DIM, int KIND>
 __global__ void __launch_bounds__(kBatchMaxBlock)
-k_batched(const Inst<R> *__restrict__ insts, const int *__restrict__ order, int n_steps, Flags F)
+k_batched(const Inst<R> *__restrict__ insts, const int *__restrict__ order, int n_steps, size_t lds_bytes, Flags F)
 {
+    extern __shared__ unsigned char smem_raw[];
     __shared__ int lds[kBatchMaxBlock / 64];
     __shared__ int s_bad, s_one;
     if (threadIdx.x == 0) { s_bad = 0; s_one = 0; }
     const Inst<R> &I = insts[order[blockIdx.x]];
     int bad = 0, one = 0;
     R s2 = signal_floor(I.Ph);
-    for (int s = 0; s < n_steps; ++s) batched_step<R, DIM>(I, lds, F.word, bad, one, s2, s == 0);
+    const int ng = I.Pg.n, nd = I.Pd.n;
+    bool fits = lds_bytes > 0 && max(ng, nd) <= kSmallOwn * int(blockDim.x) && (DIM == 1 || I.mask_rows > 0);
+    if (fits) {
+        Sorted<R> Sg, Sd;
+        CellSolve<R> *cs;
+        R *en2;
+        fits = small_carve<R, DIM, KIND>(nullptr, ng, nd, I.G.ncell, I.mask_rows, Sg, Sd, cs, en2) <= lds_bytes;
+    }
+    if (fits)
+        small_steps<R, DIM, KIND>(I.G, I.Ph, I.Pg, I.Pd, I.Sg.has_mass, I.Sd.has_mass, I.mask_rows, n_steps, smem_raw,
+                                  lds, nullptr, one, bad, s2);
+    else
+        for (int s = 0; s < n_steps; ++s) batched_step<R, DIM, KIND>(I, lds, F.word, bad, one, s2, s == 0);
     if (I.Ph.vlim2 > R(0) && s2 > I.Ph.vlim2) atomicOr(F.word, kFlagCfl);
     if (bad) atomicOr(&s_bad, 1);
     if (one) atomicAdd(&s_one, one);

@@ -177,6 +177,21 @@ Phase<R> make_phase(const tfsph_phase &ph, int dim)
     return P;
 }
 
+// The one-workgroup step evaluates every window candidate on one CU, so it is bound by
+// their number: the most of all gas particles together that still beat the launches of
+// the general step.  us a step, one workgroup against general, 2D wave (36 candidates a
+// particle): FP32 24^2 19.7 / 31.4, 32^2 25.0 / 31.2, 36^2 36.4 / 33.2; FP64 24^2 27.8 /
+// 34.2, 28^2 37.8 / 35.5.  1D waves stay below both lines (10 a particle): FP32 200 5.8 /
+// 30.5, 1500 16.4 / 31.1; FP64 200 7.3 / 30.2.
+constexpr double kSmallPairsF32 = 40000.0, kSmallPairsF64 = 24000.0;
+constexpr int kSmallSteps = 4096;        // steps per launch
+
+// Dynamic LDS of the one-workgroup step for this problem, 0 when it does not take
+// that path (small.hip).
+size_t small_step_lds(const tfsph_params *p, const tfsph_state *s);
+tfsph_status enqueue_small_steps(const tfsph_params *p, const tfsph_state *s, size_t lds, int n_steps, const Flags &F,
+                                 hipStream_t st);
+
 tfsph_status check_phase(const tfsph_phase &ph, int dim, bool need_rho, bool need_energy, const char *name);
 
 }  // namespace tfsph_host

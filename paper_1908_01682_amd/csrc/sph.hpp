@@ -758,6 +758,61 @@ __device__ __forceinline__ Own<R> own_of(const Sorted<R> &S, int a, bool with_rh
     return Own<R>{S.cell[a], S.id[a], S.pos[a], with_rho ? S.rho[a] : R(0)};
 }
 
+// Implicit update of eq. (19) for a gas particle of cell c with predictor vt, then
+// x^{n+1} = x^n + tau v^{n+1} and the carry: new velocity v, offsets o and cell cn;
+// s2 is raised to |v|^2.  False when a value is not finite.
+template <typename R, int DIM>
+__device__ __forceinline__ bool gas_advance(const Geom<R> &G, const Phys<R> &Ph, int c, const R4<R> &me, const R vt[3],
+                                            const CellSolve<R> &C, R vn[3], R on[3], int &cn, R &s2)
+{
+    const R inv = R(1) / (R(1) + C.alpha);
+    int cc[3];
+    split_cell(G, c, cc[0], cc[1], cc[2]);
+    const R oo[3] = {me.x, me.y, me.z};
+    bool ok = true;
+    R v2 = R(0);
+#pragma unroll
+    for (int d = 0; d < DIM; ++d) {
+        const R v = (vt[d] + C.alpha * C.U[d]) * inv;
+        R o = oo[d] + Ph.tau * v;
+        ok &= finite_r(v);
+        ok &= carry(o, cc[d], G.delta[d], G.nc[d]);
+        vn[d] = v;
+        on[d] = o;
+        v2 += v * v;
+    }
+    s2 = fmax(s2, v2);
+    cn = join_cell(G, cc[0], cc[1], cc[2]);
+    return ok;
+}
+
+// The same for a dust particle with velocity uu (eq. 20).
+template <typename R, int DIM>
+__device__ __forceinline__ bool dust_advance(const Geom<R> &G, const Phys<R> &Ph, int c, const R4<R> &me, const R uu[3],
+                                             const CellSolve<R> &C, R un[3], R on[3], int &cn, R &s2)
+{
+    const R inv = R(1) / (R(1) + C.beta);
+    int cc[3];
+    split_cell(G, c, cc[0], cc[1], cc[2]);
+    const R oo[3] = {me.x, me.y, me.z};
+    bool ok = true;
+    R u2 = R(0);
+#pragma unroll
+    for (int d = 0; d < DIM; ++d) {
+        const R ut = uu[d] + Ph.tau * Ph.g[d];
+        const R u = (ut + C.beta * C.V[d]) * inv;
+        R o = oo[d] + Ph.tau * u;
+        ok &= finite_r(u);
+        ok &= carry(o, cc[d], G.delta[d], G.nc[d]);
+        un[d] = u;
+        on[d] = o;
+        u2 += u * u;
+    }
+    s2 = fmax(s2, u2);
+    cn = join_cell(G, cc[0], cc[1], cc[2]);
+    return ok;
+}
+
 // Implicit update of eq. (19) for gas particle a of cell C, then
 // x^{n+1} = x^n + tau v^{n+1} and the carry; writes the caller's arrays at a
 // (and the new cell to *new_cell when given).  With use_own, `own` holds a's
@@ -769,12 +824,7 @@ __device__ __forceinline__ bool gas_finish(const Geom<R> &G, const Phys<R> &Ph, 
                                            bool use_own = false, const Own<R> &own = Own<R>{})
 {
     const int c = use_own ? own.cell : Sg.cell[a];
-    const R inv = R(1) / (R(1) + C.alpha);
-    int cc[3];
-    split_cell(G, c, cc[0], cc[1], cc[2]);
     const R4<R> me = use_own ? own.pos : Sg.pos[a];
-    const R oo[3] = {me.x, me.y, me.z};
-    bool ok = true;
     // v~ from the block's LDS copy when it has one: (m, v~x, v~y, v~z)
     R vt[3];
     if (staged) {
@@ -785,21 +835,16 @@ __device__ __forceinline__ bool gas_finish(const Geom<R> &G, const Phys<R> &Ph, 
 #pragma unroll
         for (int d = 0; d < DIM; ++d) vt[d] = Sg.vt[d][a];
     }
-    R v2 = R(0);
+    R v[3], o[3];
+    int cn;
+    const bool ok = gas_advance<R, DIM>(G, Ph, c, me, vt, C, v, o, cn, s2);
 #pragma unroll
     for (int d = 0; d < DIM; ++d) {
-        const R v = (vt[d] + C.alpha * C.U[d]) * inv;
-        R o = oo[d] + Ph.tau * v;
-        ok &= finite_r(v);
-        ok &= carry(o, cc[d], G.delta[d], G.nc[d]);
-        Pg.vel[d][a] = v;
-        Pg.off[d][a] = o;
-        v2 += v * v;
+        Pg.vel[d][a] = v[d];
+        Pg.off[d][a] = o[d];
     }
     // signal speed of eq. (4): max(|v|, c), with the sound speed of the new energy
-    s2 = fmax(s2, v2);
     if (Ph.eos != 0 && Sg.energy) s2 = fmax(s2, Ph.ggm1 * Pg.energy[a]);
-    const int cn = join_cell(G, cc[0], cc[1], cc[2]);
     Pg.cell[a] = cn;
     if (new_cell) *new_cell = cn;
     Pg.id[a] = use_own ? own.id : Sg.id[a];
@@ -817,12 +862,7 @@ __device__ __forceinline__ bool dust_finish(const Geom<R> &G, const Phys<R> &Ph,
                                             bool use_own = false, const Own<R> &own = Own<R>{})
 {
     const int c = use_own ? own.cell : Sd.cell[j];
-    const R inv = R(1) / (R(1) + C.beta);
-    int cc[3];
-    split_cell(G, c, cc[0], cc[1], cc[2]);
     const R4<R> me = use_own ? own.pos : Sd.pos[j];
-    const R oo[3] = {me.x, me.y, me.z};
-    bool ok = true;
     // u from the block's LDS copy when it has one: (m, ux, uy, uz)
     R uu[3];
     if (staged) {
@@ -833,20 +873,14 @@ __device__ __forceinline__ bool dust_finish(const Geom<R> &G, const Phys<R> &Ph,
 #pragma unroll
         for (int d = 0; d < DIM; ++d) uu[d] = Sd.vel[d][j];
     }
-    R u2 = R(0);
+    R u[3], o[3];
+    int cn;
+    const bool ok = dust_advance<R, DIM>(G, Ph, c, me, uu, C, u, o, cn, s2);
 #pragma unroll
     for (int d = 0; d < DIM; ++d) {
-        const R ut = uu[d] + Ph.tau * Ph.g[d];
-        const R u = (ut + C.beta * C.V[d]) * inv;
-        R o = oo[d] + Ph.tau * u;
-        ok &= finite_r(u);
-        ok &= carry(o, cc[d], G.delta[d], G.nc[d]);
-        Pd.vel[d][j] = u;
-        Pd.off[d][j] = o;
-        u2 += u * u;
+        Pd.vel[d][j] = u[d];
+        Pd.off[d][j] = o[d];
     }
-    s2 = fmax(s2, u2);
-    const int cn = join_cell(G, cc[0], cc[1], cc[2]);
     Pd.cell[j] = cn;
     if (new_cell) *new_cell = cn;
     Pd.id[j] = use_own ? own.id : Sd.id[j];

@@ -683,6 +683,28 @@ tfsph_status dispatch_density(tfsph_ctx *c, tfsph_state *s, int phase, hipStream
 
 }  // namespace
 
+// n_steps steps in whole-problem launches of one workgroup, where the problem is
+// small enough (small_step_lds()); done is set when they were enqueued.  Timed
+// steps and the window-scan variant keep the launches of the general path.
+static tfsph_status try_small_steps(tfsph_ctx *c, tfsph_state *s, int n_steps, hipStream_t st, bool &done)
+{
+    done = false;
+    if (c->profiling || c->variant != TFSPH_VARIANT_AUTO || n_steps < 1) return TFSPH_OK;
+    const size_t lds = small_step_lds(&c->p, s);
+    if (lds == 0) return TFSPH_OK;
+    int *partial;
+    Flags F;
+    if (c->p.precision == TFSPH_F64) {
+        Sorted<double> Sg, Sd;
+        carve_all<double>(c, Sg, Sd, partial, F);
+    } else {
+        Sorted<float> Sg, Sd;
+        carve_all<float>(c, Sg, Sd, partial, F);
+    }
+    done = true;
+    return enqueue_small_steps(&c->p, s, lds, n_steps, F, st);
+}
+
 // ----------------------------------------------------------------------------
 // public entry points
 // ----------------------------------------------------------------------------
@@ -734,6 +756,9 @@ extern "C" tfsph_status tfsph_step(tfsph_ctx *c, tfsph_state *s, int32_t n_steps
     if (r != TFSPH_OK) return r;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     c->last_stream = st;
+    bool done;
+    r = try_small_steps(c, s, n_steps, st, done);
+    if (r != TFSPH_OK || done) return r;
     for (int i = 0; i < n_steps; ++i) {
         r = c->p.precision == TFSPH_F64 ? dispatch_step<double>(c, s, st, i > 0) : dispatch_step<float>(c, s, st, i > 0);
         if (r != TFSPH_OK) return r;
@@ -903,6 +928,9 @@ extern "C" tfsph_status tfsph_step_graph(tfsph_ctx *c, tfsph_state *s, int32_t n
     if (r != TFSPH_OK) return r;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     c->last_stream = st;
+    bool done;
+    r = try_small_steps(c, s, n_steps, st, done);      // one launch: nothing to replay
+    if (r != TFSPH_OK || done) return r;
     const int n_full = n_steps / chunk, rem = n_steps % chunk;
     if (n_full > 0) {
         const unsigned long long key = state_key(s, chunk);
@@ -1017,7 +1045,10 @@ extern "C" tfsph_status tfsph_step_noalloc(const tfsph_params *p, tfsph_state *s
     c.cells_per_block = default_cells_per_block(p->dim);
     r = p->precision == TFSPH_F64 ? enqueue_init<double>(&c, s, st) : enqueue_init<float>(&c, s, st);
     if (r != TFSPH_OK) return r;
-    for (int i = 0; i < n_steps; ++i) {
+    bool done;
+    r = try_small_steps(&c, s, n_steps, st, done);
+    if (r != TFSPH_OK) return r;
+    for (int i = 0; i < n_steps && !done; ++i) {
         r = p->precision == TFSPH_F64 ? dispatch_step<double>(&c, s, st, i > 0) : dispatch_step<float>(&c, s, st, i > 0);
         if (r != TFSPH_OK) return r;
     }
