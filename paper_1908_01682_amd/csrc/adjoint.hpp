@@ -243,7 +243,7 @@ k_adj_force(Geom<R> G, Phys<R> Ph, Sorted<R> Sg, const R *abar0, const R *abar1,
     const R *abar[3] = {abar0, abar1, abar2};
     R *xacc[3] = {xacc0, xacc1, xacc2};
     int cx, cy, cz;
-    split_cell(G, Sg.cell[a], cx, cy, cz);
+    cell_coords<DIM>(G, Sg.cell[a], cx, cy, cz);
     const R4<R> me = Sg.frc[a];
     const R oa[3] = {me.x, me.y, me.z};
     const R Pa = me.w;
@@ -296,7 +296,7 @@ k_adj_density(Geom<R> G, Sorted<R> S, const R *rhobar, R *xacc0, R *xacc1, R *xa
     if (a >= S.n) return;
     R *xacc[3] = {xacc0, xacc1, xacc2};
     int cx, cy, cz;
-    split_cell(G, S.cell[a], cx, cy, cz);
+    cell_coords<DIM>(G, S.cell[a], cx, cy, cz);
     const R4<R> me = S.pos[a];
     const R oa[3] = {me.x, me.y, me.z};
     const R ma = me.w;

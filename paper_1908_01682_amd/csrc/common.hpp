@@ -131,6 +131,8 @@ struct Geom {
     R support2;          // (2h)^2
     R wnorm;             // sigma_d / h^d
     R gnorm;             // sigma_d / h^(d+1)
+    unsigned div_mul[2]; // nc[0], nc[1] as divisors (divide_by()); 0: the divisor is 1
+    int div_shift[2];
 };
 
 // Physics of the step: EOS, drag, time step, viscosity.
@@ -249,6 +251,35 @@ __device__ __forceinline__ int wrap_index(int c, int n)
     return c < 0 ? c + n : c;
 }
 
+// Into [0, n) from at most one period away: neighbour windows reach at most W cells
+// beyond the grid and a grid has at least 2 W + 1 cells per axis.
+__device__ __forceinline__ int wrap_once(int c, int n)
+{
+    return c < 0 ? c + n : (c >= n ? c - n : c);
+}
+
+// x / n for 0 <= x < 2^31 by a multiplication.  With s = ceil(log2 n), at least 1, and
+// mul = ceil(2^(31 + s) / n) the excess mul n - 2^(31 + s) is below 2^s, so
+// x mul / 2^(31 + s) lies within [x / n, x / n + 1 / n) and its floor is the quotient.
+// mul = 0 stands for n = 1.  (A division by a run-time integer is about 25
+// instructions; a particle needs up to four to find its cell's coordinates.)
+__host__ __device__ inline int divide_by(int x, unsigned mul, int shift)
+{
+    const unsigned hi = unsigned((uint64_t(unsigned(x)) * mul) >> 32);
+    return mul ? int(hi >> shift) : x;
+}
+
+inline void make_divisor(int n, unsigned &mul, int &shift)
+{
+    mul = 0;
+    shift = 0;
+    if (n < 2) return;
+    int s = 1;
+    while ((int64_t(1) << s) < n) ++s;
+    mul = unsigned(((uint64_t(1) << (31 + s)) + uint64_t(n) - 1) / uint64_t(n));
+    shift = s - 1;
+}
+
 template <typename R>
 __device__ __forceinline__ bool finite_r(R x)
 {
@@ -280,7 +311,7 @@ __device__ __forceinline__ bool carry(R &o, int &c, R D, int n)
     for (int it = 0; it < 8 && o < R(0); ++it) { o += D; c -= 1; }
     for (int it = 0; it < 8 && o >= D; ++it) { o -= D; c += 1; }
     if (o < R(0) || o >= D) { o = R(0); ok = false; }
-    c = wrap_index(c, n);
+    if (c < 0 || c >= n) c = wrap_index(c, n);
     return ok;
 }
 
@@ -291,6 +322,23 @@ __device__ __forceinline__ void split_cell(const Geom<R> &G, int lin, int &cx, i
     const int r = lin / G.nc[0];
     cy = r % G.nc[1];
     cz = r / G.nc[1];
+}
+
+// The same for a valid cell index (0 <= lin < ncell) of a DIM-dimensional grid
+template <int DIM, typename R>
+__device__ __forceinline__ void cell_coords(const Geom<R> &G, int lin, int &cx, int &cy, int &cz)
+{
+    cx = lin;
+    cy = cz = 0;
+    if constexpr (DIM > 1) {
+        const int r = divide_by(lin, G.div_mul[0], G.div_shift[0]);
+        cx = lin - r * G.nc[0];
+        cy = r;
+        if constexpr (DIM > 2) {
+            cz = divide_by(r, G.div_mul[1], G.div_shift[1]);
+            cy = r - cz * G.nc[1];
+        }
+    }
 }
 
 template <typename R>

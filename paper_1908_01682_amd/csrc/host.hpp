@@ -122,6 +122,7 @@ Geom<R> make_geom(const tfsph_params *p)
         G.win[d] = d < p->dim ? window_of(p, d) : 0;
         G.delta[d] = d < p->dim ? R((p->box_hi[d] - p->box_lo[d]) / p->n_cells[d]) : R(1);
     }
+    for (int d = 0; d < 2; ++d) make_divisor(G.nc[d], G.div_mul[d], G.div_shift[d]);
     G.h = R(p->h);
     G.inv_h = R(1.0 / p->h);
     G.support2 = R(4.0 * p->h * p->h);

@@ -62,7 +62,7 @@ k_imex_gas1(Geom<R> G, Phys<R> Ph, Sorted<R> S, Stage<R> X, Phase<R> Q, ImexCoef
     R acc[3], dedt;
     gas_force_at<R, DIM, KIND>(G, Ph, S, a, acc, dedt);
     int cc[3];
-    split_cell(G, c0, cc[0], cc[1], cc[2]);
+    cell_coords<DIM>(G, c0, cc[0], cc[1], cc[2]);
     const R oo[3] = {me.x, me.y, me.z};
     bool ok = true;
 #pragma unroll
@@ -94,7 +94,7 @@ __global__ void __launch_bounds__(kBlock) k_imex_dust1(Geom<R> G, Phys<R> Ph, So
     const int j = blockIdx.x * kBlock + threadIdx.x;
     if (j >= S.n) return;
     int cc[3];
-    split_cell(G, S.cell[j], cc[0], cc[1], cc[2]);
+    cell_coords<DIM>(G, S.cell[j], cc[0], cc[1], cc[2]);
     const R4<R> me = S.pos[j];
     const R oo[3] = {me.x, me.y, me.z};
     bool ok = true;
@@ -152,7 +152,7 @@ k_imex_stage3(Geom<R> G, Phys<R> Ph, Sorted<R> Sg, Sorted<R> Sd, Stage<R> Xg, St
     const Phase<R> &Q = gas ? Qg : Qd;
     if (i >= S.n) return;
     int cc[3];
-    split_cell(G, S.cell[i], cc[0], cc[1], cc[2]);
+    cell_coords<DIM>(G, S.cell[i], cc[0], cc[1], cc[2]);
     const R4<R> me = S.pos[i];
     const R oo[3] = {me.x, me.y, me.z};
     bool ok = true;

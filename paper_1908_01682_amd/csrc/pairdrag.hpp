@@ -131,7 +131,7 @@ __device__ __forceinline__ bool store_moved(const Geom<R> &G, const Phys<R> &Ph,
                                             bool has_mass)
 {
     int cc[3];
-    split_cell(G, cell, cc[0], cc[1], cc[2]);
+    cell_coords<DIM>(G, cell, cc[0], cc[1], cc[2]);
     const R oo[3] = {me.x, me.y, me.z};
     bool ok = true;
     R v2 = R(0);
@@ -167,7 +167,7 @@ k_pair_gas(Geom<R> G, Phys<R> Ph, Sorted<R> Sg, Sorted<R> Sd, const R4<R> *__res
         const R vt[3] = {Sg.vt[0][a], DIM > 1 ? Sg.vt[1][a] : R(0), DIM > 2 ? Sg.vt[2][a] : R(0)};
         const int cell = Sg.cell[a], id = Sg.id[a];
         int cx, cy, cz;
-        split_cell(G, cell, cx, cy, cz);
+        cell_coords<DIM>(G, cell, cx, cy, cz);
         const R4<R> me = Sg.pos[a];
         const R oa[3] = {me.x, me.y, me.z};
         const R rho_a = Sg.rho[a];
@@ -250,7 +250,7 @@ k_pair_dust(Geom<R> G, Phys<R> Ph, Sorted<R> Sg, Sorted<R> Sd, const R4<R> *__re
     if (j < Sd.n) {
         const int cell = Sd.cell[j], id = Sd.id[j];
         int cx, cy, cz;
-        split_cell(G, cell, cx, cy, cz);
+        cell_coords<DIM>(G, cell, cx, cy, cz);
         const R4<R> me = Sd.pos[j];
         const R oj[3] = {me.x, me.y, me.z};
         const R uj[3] = {Sd.vel[0][j], DIM > 1 ? Sd.vel[1][j] : R(0), DIM > 2 ? Sd.vel[2][j] : R(0)};

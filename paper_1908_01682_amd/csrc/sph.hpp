@@ -63,7 +63,7 @@ __device__ __forceinline__ void row_ranges(const Geom<R> &G, int cx, int row, co
 {
 #pragma unroll
     for (int k = 0; k <= 2 * WX; ++k) {
-        const int lin = wrap_index(cx - WX + k, G.nc[0]) + row;
+        const int lin = wrap_once(cx - WX + k, G.nc[0]) + row;
         bs[k] = start[lin];
         be[k] = start[lin + 1];
     }
@@ -108,8 +108,8 @@ __device__ __forceinline__ void for_window_pairs(const Geom<R> &G, int cx, int c
             }
             int dy, dz;
             row_offsets(l, wy, wz, dy, dz);
-            const int z = DIM > 2 ? wrap_index(cz + dz, G.nc[2]) : 0;
-            const int y = DIM > 1 ? wrap_index(cy + dy, G.nc[1]) : 0;
+            const int z = DIM > 2 ? wrap_once(cz + dz, G.nc[2]) : 0;
+            const int y = DIM > 1 ? wrap_once(cy + dy, G.nc[1]) : 0;
             rz0[t] = DIM > 2 ? T(oa[2]) - T(dz) * T(G.delta[2]) : T(0);
             ry0[t] = DIM > 1 ? T(oa[1]) - T(dy) * T(G.delta[1]) : T(0);
             row_ranges<WX>(G, cx, G.nc[0] * (y + G.nc[1] * z), start, bs[t], be[t]);
@@ -169,13 +169,13 @@ __device__ __forceinline__ void for_window(const Geom<R> &G, int cx, int cy, int
             if (t == 1 && l == i) break;
             int dy, dz;
             row_offsets(l, wy, wz, dy, dz);
-            const int z = DIM > 2 ? wrap_index(cz + dz, G.nc[2]) : 0;
+            const int z = DIM > 2 ? wrap_once(cz + dz, G.nc[2]) : 0;
             const T rz0 = DIM > 2 ? T(oa[2]) - T(dz) * T(G.delta[2]) : T(0);
-            const int y = DIM > 1 ? wrap_index(cy + dy, G.nc[1]) : 0;
+            const int y = DIM > 1 ? wrap_once(cy + dy, G.nc[1]) : 0;
             const T ry0 = DIM > 1 ? T(oa[1]) - T(dy) * T(G.delta[1]) : T(0);
             const int row = G.nc[0] * (y + G.nc[1] * z);
             for (int dx = -wx; dx <= wx; ++dx) {
-                const int lin = wrap_index(cx + dx, G.nc[0]) + row;
+                const int lin = wrap_once(cx + dx, G.nc[0]) + row;
                 const T rx0 = T(oa[0]) - T(dx) * T(G.delta[0]);
                 visit_range<R, DIM, true, T>(start[lin], start[lin + 1], data, rx0, ry0, rz0, fn);
             }
@@ -395,7 +395,7 @@ __device__ __forceinline__ R density_at(const Geom<R> &G, const Sorted<R> &S, in
                                         R4<R> *own = nullptr)
 {
     int cx, cy, cz;
-    split_cell(G, S.cell[a], cx, cy, cz);
+    cell_coords<DIM>(G, S.cell[a], cx, cy, cz);
     const R4<R> me = S.pos[a];
     if (own) *own = me;
     const R oa[3] = {me.x, me.y, me.z};
@@ -487,7 +487,7 @@ __device__ __forceinline__ void gas_force_at(const Geom<R> &G, const Phys<R> &Ph
     using T = typename ForceArith<R>::T;
     using A = typename ForceArith<R>::A;
     int cx, cy, cz;
-    split_cell(G, S.cell[a], cx, cy, cz);
+    cell_coords<DIM>(G, S.cell[a], cx, cy, cz);
     const R4<R> *pos = S.pos;
     const T mu_m = S.pos[a].w;        // uniform mass (kForceIsoUniform)
     const T inv_h = G.inv_h;
@@ -767,7 +767,7 @@ __device__ __forceinline__ bool gas_advance(const Geom<R> &G, const Phys<R> &Ph,
 {
     const R inv = R(1) / (R(1) + C.alpha);
     int cc[3];
-    split_cell(G, c, cc[0], cc[1], cc[2]);
+    cell_coords<DIM>(G, c, cc[0], cc[1], cc[2]);
     const R oo[3] = {me.x, me.y, me.z};
     bool ok = true;
     R v2 = R(0);
@@ -793,7 +793,7 @@ __device__ __forceinline__ bool dust_advance(const Geom<R> &G, const Phys<R> &Ph
 {
     const R inv = R(1) / (R(1) + C.beta);
     int cc[3];
-    split_cell(G, c, cc[0], cc[1], cc[2]);
+    cell_coords<DIM>(G, c, cc[0], cc[1], cc[2]);
     const R oo[3] = {me.x, me.y, me.z};
     bool ok = true;
     R u2 = R(0);
