@@ -6,6 +6,7 @@
 #include "binning.hpp"
 #include "host.hpp"
 #include "sph.hpp"
+#include "tiles.hpp"
 
 namespace tfsph_host {
 
@@ -61,14 +62,20 @@ inline tfsph_status enqueue_bin(int ng, int nd, const Geom<R> &G, const Phase<R>
 }
 
 
-// kernel variant: 0 (auto) and 1 = global-memory pair loops (neighbour masks
-// when S.nmask is set)
+// kernel variant: 0 (auto) takes the matrix-core support test where the window
+// allows it; 1 = window scans (neighbour masks when S.nmask is set)
 template <typename R, int DIM>
 inline tfsph_status enqueue_density(const Geom<R> &G, const Phys<R> &Ph, const Sorted<R> &S, int want_frc,
                                     hipStream_t st, int variant = 0)
 {
-    (void)variant;
     if (S.n == 0) return TFSPH_OK;
+    if constexpr (DIM == 3) {
+        if (variant == TFSPH_VARIANT_AUTO && tile_windows(G)) {
+            hipLaunchKernelGGL((k_density_tiles<R>), dim3(blocks_for(S.n)), dim3(kBlock), 0, st, G, Ph, S, want_frc);
+            LAUNCH_CHECK("density_tiles");
+            return TFSPH_OK;
+        }
+    }
     hipLaunchKernelGGL((k_density<R, DIM>), dim3(blocks_for(S.n)), dim3(kBlock), 0, st, G, Ph, S, want_frc);
     LAUNCH_CHECK("density");
     return TFSPH_OK;

@@ -30,6 +30,7 @@
 #pragma once
 
 #include "sph.hpp"
+#include "tiles.hpp"
 
 namespace tfsph {
 
@@ -59,11 +60,17 @@ __global__ void __launch_bounds__(kBlock) k_pack_vel_rho(Sorted<R> S, R4<R> *vr)
 // to fn (walk_bits()); a pair of rows with more than kMaskBits candidates is
 // handed over whole.  Every pair term vanishes exactly for q >= 2 (W = W' =
 // 0), so the sums are those of for_window().  Windows wider than 2 cells
-// along x use for_window().
-template <typename R, int DIM, typename Fn>
+// along x use for_window().  With TILES (3D, tile_windows()) the bits come from
+// the matrix-core test instead of the scan; every lane of the wave must call it.
+template <typename R, int DIM, bool TILES, typename Fn>
 __device__ __forceinline__ void for_support(const Geom<R> &G, int cx, int cy, int cz, const R oa[3],
-                                            const int *__restrict__ start, const R4<R> *__restrict__ data, Fn &&fn)
+                                            const int *__restrict__ start, const int *__restrict__ cell,
+                                            const R4<R> *__restrict__ data, Fn &&fn)
 {
+    if constexpr (TILES) {
+        for_tile_support<R>(G, cx, cy, cz, oa, start, cell, data, nullptr, 0, false, fn);
+        return;
+    }
     const R cut = R(kMaskQ) * G.h;
     const R cut2 = cut * cut;
     auto inside = [&](int, const R4<R> &, R rx, R ry, R rz, bool ok) {
@@ -155,15 +162,18 @@ __device__ __forceinline__ bool store_moved(const Geom<R> &G, const Phys<R> &Ph,
 // One gas particle of MK or ISPH after the explicit gas pass of the IDIC
 // step (k_gas_predict: the predictor v~ = v + tau (A + g) in Sg.vt, the new
 // energy in the caller's array): the drag from the dust window, update, move.
-template <typename R, int DIM, int SCHEME>
-__global__ void __launch_bounds__(kBlock)
+template <typename R, int DIM, int SCHEME, bool TILES>
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(TILES ? (sizeof(R) == 4 ? 4 : 3) : 1)))
 k_pair_gas(Geom<R> G, Phys<R> Ph, Sorted<R> Sg, Sorted<R> Sd, const R4<R> *__restrict__ vrd, Phase<R> Pg,
            Flags F)
 {
-    const int a = xcd_block(gridDim.x) * kBlock + threadIdx.x;
+    // every lane takes part in the tile test: lanes past the end repeat the last particle
+    const int a0 = xcd_block(gridDim.x) * kBlock + threadIdx.x;
+    const bool live = a0 < Sg.n;
+    const int a = live ? a0 : Sg.n - 1;
     R s2 = signal_floor(Ph);
     int bad = 0, lonely = 0;
-    if (a < Sg.n) {
+    if (TILES || live) {
         const R vt[3] = {Sg.vt[0][a], DIM > 1 ? Sg.vt[1][a] : R(0), DIM > 2 ? Sg.vt[2][a] : R(0)};
         const int cell = Sg.cell[a], id = Sg.id[a];
         int cx, cy, cz;
@@ -178,7 +188,7 @@ k_pair_gas(Geom<R> G, Phys<R> Ph, Sorted<R> Sg, Sorted<R> Sd, const R4<R> *__res
             const R eta2 = R(0.001) * G.h * G.h;
             const R inv_rho_a = R(1) / rho_a;
             R dx = R(0), dy = R(0), dz = R(0);
-            for_support<R, DIM>(G, cx, cy, cz, oa, Sd.start, Sd.pos, [&](int b, const R4<R> &q, R rx, R ry, R rz, bool ok) {
+            for_support<R, DIM, TILES>(G, cx, cy, cz, oa, Sd.start, Sd.cell, Sd.pos, [&](int b, const R4<R> &q, R rx, R ry, R rz, bool ok) {
                 if (!ok) return;
                 const R r2 = rx * rx + ry * ry + rz * rz;
                 const R w = spline_f(fsqrt(r2) * G.inv_h);
@@ -197,7 +207,7 @@ k_pair_gas(Geom<R> G, Phys<R> Ph, Sorted<R> Sg, Sorted<R> Sd, const R4<R> *__res
             for (int d = 0; d < DIM; ++d) vn[d] = vt[d] + Ph.tau * dr[d];
         } else {
             R rd = R(0), ux = R(0), uy = R(0), uz = R(0);
-            for_support<R, DIM>(G, cx, cy, cz, oa, Sd.start, Sd.pos, [&](int b, const R4<R> &q, R rx, R ry, R rz, bool ok) {
+            for_support<R, DIM, TILES>(G, cx, cy, cz, oa, Sd.start, Sd.cell, Sd.pos, [&](int b, const R4<R> &q, R rx, R ry, R rz, bool ok) {
                 if (!ok) return;
                 const R r2 = rx * rx + ry * ry + rz * rz;
                 const R mw = q.w * spline_f(fsqrt(r2) * G.inv_h);
@@ -216,7 +226,7 @@ k_pair_gas(Geom<R> G, Phys<R> Ph, Sorted<R> Sg, Sorted<R> Sd, const R4<R> *__res
                 alpha = Ph.tau * K / rho_a;
                 beta = Ph.tau * K / rd;
             } else {
-                lonely = 1;
+                lonely = live ? 1 : 0;
             }
             const R D = R(1) + alpha + beta;
 #pragma unroll
@@ -225,8 +235,10 @@ k_pair_gas(Geom<R> G, Phys<R> Ph, Sorted<R> Sg, Sorted<R> Sd, const R4<R> *__res
                 vn[d] = ((R(1) + beta) * vt[d] + alpha * ut) / D;
             }
         }
-        if (Sg.energy && Ph.eos != 0) s2 = fmax(s2, Ph.ggm1 * Pg.energy[a]);
-        bad = !store_moved<R, DIM>(G, Ph, Pg, a, cell, id, me, rho_a, vn, s2, Sg.has_mass);
+        if (live) {
+            if (Sg.energy && Ph.eos != 0) s2 = fmax(s2, Ph.ggm1 * Pg.energy[a]);
+            bad = !store_moved<R, DIM>(G, Ph, Pg, a, cell, id, me, rho_a, vn, s2, Sg.has_mass);
+        }
     }
     publish_speed(Ph, F, s2);
     if (bad) atomicOr(F.word, 1u);
@@ -239,15 +251,17 @@ k_pair_gas(Geom<R> G, Phys<R> Ph, Sorted<R> Sg, Sorted<R> Sd, const R4<R> *__res
 // One dust particle of MK or ISPH: the drag (MK) or the interpolated gas state
 // and pressure gradient (ISPH) from the gas window, update, move.  ISPH walks
 // the gas records frc = (ox, oy, oz, P = p / rho^2) of the density pass.
-template <typename R, int DIM, int SCHEME>
-__global__ void __launch_bounds__(kBlock)
+template <typename R, int DIM, int SCHEME, bool TILES>
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(TILES ? (sizeof(R) == 4 ? 4 : 3) : 1)))
 k_pair_dust(Geom<R> G, Phys<R> Ph, Sorted<R> Sg, Sorted<R> Sd, const R4<R> *__restrict__ vrg, Phase<R> Pd,
             Flags F)
 {
-    const int j = xcd_block(gridDim.x) * kBlock + threadIdx.x;
+    const int j0 = xcd_block(gridDim.x) * kBlock + threadIdx.x;
+    const bool live = j0 < Sd.n;
+    const int j = live ? j0 : Sd.n - 1;
     R s2 = signal_floor(Ph);
     int bad = 0, lonely = 0;
-    if (j < Sd.n) {
+    if (TILES || live) {
         const int cell = Sd.cell[j], id = Sd.id[j];
         int cx, cy, cz;
         cell_coords<DIM>(G, cell, cx, cy, cz);
@@ -260,7 +274,7 @@ k_pair_dust(Geom<R> G, Phys<R> Ph, Sorted<R> Sg, Sorted<R> Sd, const R4<R> *__re
             const R eta2 = R(0.001) * G.h * G.h;
             const R inv_rho_j = R(1) / rho_j;
             R dx = R(0), dy = R(0), dz = R(0);
-            for_support<R, DIM>(G, cx, cy, cz, oj, Sg.start, Sg.pos, [&](int b, const R4<R> &q, R rx, R ry, R rz, bool ok) {
+            for_support<R, DIM, TILES>(G, cx, cy, cz, oj, Sg.start, Sg.cell, Sg.pos, [&](int b, const R4<R> &q, R rx, R ry, R rz, bool ok) {
                 if (!ok) return;
                 const R r2 = rx * rx + ry * ry + rz * rz;
                 const R w = spline_f(fsqrt(r2) * G.inv_h);
@@ -280,7 +294,7 @@ k_pair_dust(Geom<R> G, Phys<R> Ph, Sorted<R> Sg, Sorted<R> Sd, const R4<R> *__re
         } else {
             R rg = R(0), pj = R(0), vx = R(0), vy = R(0), vz = R(0);
             R gp[3] = {R(0), R(0), R(0)}, g1[3] = {R(0), R(0), R(0)};
-            for_support<R, DIM>(G, cx, cy, cz, oj, Sg.start, Sg.frc, [&](int b, const R4<R> &q, R rx, R ry, R rz, bool ok) {
+            for_support<R, DIM, TILES>(G, cx, cy, cz, oj, Sg.start, Sg.cell, Sg.frc, [&](int b, const R4<R> &q, R rx, R ry, R rz, bool ok) {
                 if (!ok) return;
                 const R r2 = rx * rx + ry * ry + rz * rz;
                 const R r = fsqrt(r2);
@@ -315,7 +329,7 @@ k_pair_dust(Geom<R> G, Phys<R> Ph, Sorted<R> Sg, Sorted<R> Sd, const R4<R> *__re
                 alpha = Ph.tau * K / rg;
                 beta = Ph.tau * K / rho_j;
             } else {
-                lonely = 1;
+                lonely = live ? 1 : 0;
             }
             const R D = R(1) + alpha + beta;
 #pragma unroll
@@ -325,7 +339,7 @@ k_pair_dust(Geom<R> G, Phys<R> Ph, Sorted<R> Sg, Sorted<R> Sd, const R4<R> *__re
                 un[d] = (beta * vt + (R(1) + alpha) * ut) / D;
             }
         }
-        bad = !store_moved<R, DIM>(G, Ph, Pd, j, cell, id, me, rho_j, un, s2, Sd.has_mass);
+        if (live) bad = !store_moved<R, DIM>(G, Ph, Pd, j, cell, id, me, rho_j, un, s2, Sd.has_mass);
     }
     publish_speed(Ph, F, s2);
     if (bad) atomicOr(F.word, 1u);

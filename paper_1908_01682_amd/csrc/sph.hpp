@@ -385,6 +385,17 @@ __device__ __forceinline__ R sound_of(const Phys<R> &Ph, R e)
     return Ph.eos == 0 ? Ph.cs : sqrt(Ph.ggm1 * e);
 }
 
+// one candidate's term of the summation density; returns its q = r / h
+template <typename R>
+__device__ __forceinline__ R density_add(const Geom<R> &G, const R4<R> &q, R rx, R ry, R rz, bool ok, R &acc)
+{
+    const R r2 = rx * rx + ry * ry + rz * rz;
+    const R qq = fsqrt(r2) * G.inv_h;
+    const R m = ok ? q.w : R(0);
+    acc += m * spline_f(qq);
+    return qq;
+}
+
 // --------------------------------------------------------------------------
 // Summation density of phase S at its own sorted particle a.  With `record`
 // (gas, masks allocated) the neighbour mask rows of a are stored as well; with
@@ -401,10 +412,7 @@ __device__ __forceinline__ R density_at(const Geom<R> &G, const Sorted<R> &S, in
     const R oa[3] = {me.x, me.y, me.z};
     R acc = R(0);
     auto term = [&](int, const R4<R> &q, R rx, R ry, R rz, bool ok) {
-        const R r2 = rx * rx + ry * ry + rz * rz;
-        const R qq = fsqrt(r2) * G.inv_h;
-        const R m = ok ? q.w : R(0);
-        acc += m * spline_f(qq);
+        const R qq = density_add(G, q, rx, ry, rz, ok, acc);
         return ok && qq < R(kMaskQ);
     };
     if (record && S.nmask)
@@ -412,6 +420,19 @@ __device__ __forceinline__ R density_at(const Geom<R> &G, const Sorted<R> &S, in
     else
         for_window<R, DIM>(G, cx, cy, cz, oa, S.start, S.pos, term);
     return acc * G.wnorm;
+}
+
+// density rho of particle a (its record me) into S.rho[a]; with want_frc also the
+// force-pass record (ox, oy, oz, p / rho^2)
+template <typename R>
+__device__ __forceinline__ void density_finish(const Geom<R> &G, const Phys<R> &Ph, const Sorted<R> &S, int a,
+                                               const R4<R> &me, R rho, int want_frc)
+{
+    S.rho[a] = rho;
+    if (want_frc) {
+        const R e = S.energy ? S.energy[a] : R(0);
+        S.frc[a] = mk4<R>(me.x, me.y, me.z, pressure_of(Ph, rho, e) / (rho * rho));
+    }
 }
 
 // density of particle a into S.rho[a]; with want_frc also the force-pass
@@ -422,11 +443,7 @@ __device__ __forceinline__ void density_store(const Geom<R> &G, const Phys<R> &P
 {
     R4<R> me;
     const R rho = density_at<R, DIM>(G, S, a, want_frc != 0, &me);
-    S.rho[a] = rho;
-    if (want_frc) {
-        const R e = S.energy ? S.energy[a] : R(0);
-        S.frc[a] = mk4<R>(me.x, me.y, me.z, pressure_of(Ph, rho, e) / (rho * rho));
-    }
+    density_finish<R>(G, Ph, S, a, me, rho, want_frc);
 }
 
 // Block-to-work map.  Consecutive block ids land on different XCDs

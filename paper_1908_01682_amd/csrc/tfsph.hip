@@ -542,7 +542,7 @@ tfsph_status enqueue_step_pair(tfsph_ctx *c, tfsph_state *s, hipStream_t st)
         LAUNCH_CHECK("pack_vel_rho");
     }
     if (c->nd > 0) {
-        r = enqueue_density<R, DIM>(G, Ph, Sd, 0, st, 0);
+        r = enqueue_density<R, DIM>(G, Ph, Sd, 0, st, c->variant);
         if (r != TFSPH_OK) return r;
         hipLaunchKernelGGL((k_pack_vel_rho<R, DIM>), dim3(blocks_for(c->nd)), dim3(kBlock), 0, st, Sd, VR.dust);
         LAUNCH_CHECK("pack_vel_rho");
@@ -553,16 +553,23 @@ tfsph_status enqueue_step_pair(tfsph_ctx *c, tfsph_state *s, hipStream_t st)
     if (r != TFSPH_OK) return r;
     MARK(TFSPH_KERNEL_FORCE);
     MARK(TFSPH_KERNEL_UPDATE);
-    if (c->ng > 0) {
-        hipLaunchKernelGGL((k_pair_gas<R, DIM, SCHEME>), dim3(blocks_for(c->ng)), dim3(kBlock), 0, st, G, Ph, Sg, Sd,
-                           VR.dust, Pg, F);
-        LAUNCH_CHECK("pair_gas");
+    // the support of the other phase from the matrix-core test where the window allows it
+    auto drag = [&](auto tiles) {
+        constexpr bool T = decltype(tiles)::value != 0;
+        if (c->ng > 0)
+            hipLaunchKernelGGL((k_pair_gas<R, DIM, SCHEME, T>), dim3(blocks_for(c->ng)), dim3(kBlock), 0, st, G, Ph, Sg,
+                               Sd, VR.dust, Pg, F);
+        if (c->nd > 0)
+            hipLaunchKernelGGL((k_pair_dust<R, DIM, SCHEME, T>), dim3(blocks_for(c->nd)), dim3(kBlock), 0, st, G, Ph,
+                               Sg, Sd, VR.gas, Pd, F);
+    };
+    bool tiles = false;
+    if constexpr (DIM == 3) {
+        tiles = c->variant == TFSPH_VARIANT_AUTO && tile_windows(G);
+        if (tiles) drag(IntC<1>{});
     }
-    if (c->nd > 0) {
-        hipLaunchKernelGGL((k_pair_dust<R, DIM, SCHEME>), dim3(blocks_for(c->nd)), dim3(kBlock), 0, st, G, Ph, Sg, Sd,
-                           VR.gas, Pd, F);
-        LAUNCH_CHECK("pair_dust");
-    }
+    if (!tiles) drag(IntC<0>{});
+    LAUNCH_CHECK("pair_gas / pair_dust");
     MARK(TFSPH_KERNEL_UPDATE);
     return TFSPH_OK;
 }
