@@ -338,13 +338,17 @@ k_density_tiles(Geom<R> G, Phys<R> Ph, Sorted<R> S, int want_frc)
     density_finish<R>(G, Ph, S, a, me, acc * G.wnorm, want_frc);
 }
 
-// Whether a 3D problem takes the tile path: a window of one cell per axis whose
-// cells are at most four smoothing lengths wide (coarser cells would widen the
-// rounding bound, and scans of such windows are rare).
+// Whether the n candidates of a 3D problem take the tile path: a window of one cell
+// per axis, cells at most four smoothing lengths wide (coarser ones would widen the
+// rounding bound, and scans of such windows are rare), and on average at most 55
+// candidates per pair of rows (6 cells): near kMaskBits = 64 many pairs are visited
+// whole and the test is wasted.  IDIC step, us, tiles / scan: 2.2^3 particles per cell
+// (64 per pair) 138.5 / 131.1, 2.1^3 (56) 114.4 / 113.5 (MK 238 / 259), 2.05^3 (51)
+// 104.7 / 110.8.
 template <typename R>
-inline bool tile_windows(const Geom<R> &G)
+inline bool tile_windows(const Geom<R> &G, int n)
 {
-    if (G.dim != 3) return false;
+    if (G.dim != 3 || 6.0 * n > 55.0 * G.ncell) return false;
     for (int d = 0; d < 3; ++d)
         if (G.win[d] != 1 || G.delta[d] > R(4) * G.h) return false;
     return true;

@@ -1,8 +1,9 @@
 """The matrix-core support test of the 3D pair kernels against the window scans (the scan variant):
 bitwise the same states for every scheme, on grids and populations at its edges: three cells along an
 axis (every wave's window wraps), rows of cells shorter and longer than a half wave, empty cells and
-wide runs of cells, crowded cells (pairs of rows beyond 64 candidates, runs beyond the tile limit),
-cells from one support radius to four smoothing lengths wide, and particles on cell faces."""
+wide runs of cells, crowded cells (pairs of rows beyond 64 candidates, runs beyond the tile limit,
+averages on either side of the dispatch line), cells from one support radius to four smoothing
+lengths wide, and particles on cell faces."""
 import numpy as np
 import pytest
 
@@ -47,6 +48,7 @@ CASES = {
     "clumped_tiny": dict(cells=(3, 3, 4), n_gas=900, n_dust=700, width=2.0, seed=6, clump=0.9),
     "wide_cells": dict(cells=(4, 5, 3), n_gas=1500, n_dust=1500, width=4.0, seed=7),
     "on_faces": dict(cells=(9, 7, 6), n_gas=3000, n_dust=2999, width=2.0, seed=8, faces=True),
+    "full_pairs": dict(cells=(6, 5, 5), n_gas=1420, n_dust=1430, width=2.0, seed=10),
     "one_gas": dict(cells=(6, 6, 6), n_gas=1, n_dust=63, width=2.0, seed=9),
 }
 
