@@ -33,7 +33,7 @@ struct InstLayout {
 
 template <typename R>
 size_t batch_bytes(const std::vector<InstLayout> &L, int dim, Carver &cv, std::vector<Inst<R>> *table,
-                   const tfsph_batch_desc *desc, const tfsph_state *packed)
+                   const tfsph_batch_desc *desc, const tfsph_state *packed, bool line)
 {
     const int n = (int)L.size();
     Inst<R> *dev_table = cv.take<Inst<R>>(n);
@@ -51,7 +51,7 @@ size_t batch_bytes(const std::vector<InstLayout> &L, int dim, Carver &cv, std::v
     int2 *tab_cells = cv.take<int2>(cells);
     (void)dev_table, (void)order, (void)word, (void)one, (void)tab_part, (void)tab_cells;
     for (int i = 0; i < n; ++i) {
-        PhaseFlags fg{L[i].mass_g, false, true}, fd{L[i].mass_d, false, false};
+        PhaseFlags fg{L[i].mass_g, false, true, 0, line}, fd{L[i].mass_d, false, false, 0, line};
         Sorted<R> Sg = carve_phase<R>(cv, L[i].ng, dim, L[i].ncell, fg);
         Sorted<R> Sd = carve_phase<R>(cv, L[i].nd, dim, L[i].ncell, fd);
         CellSolve<R> *cs = cv.take<CellSolve<R>>(L[i].ncell);
@@ -145,6 +145,7 @@ struct tfsph_batch {
     int flat_cpb = 0;              // cells per block of the flattened form's update launch
     std::vector<int3> host_small;  // (gas, dust, cells) of every instance; cells 0: never in LDS
     int host_mask_rows = 0;        // most neighbour mask words per particle of any instance (2D)
+    bool line = false;             // 1D: the flattened form runs the fused step (line.hpp)
     int flat_kind = -1;            // force-loop kind of every instance (kForce*), -1 if they differ
     FlatTable flat{};
     int flat_blocks_g = 0, flat_blocks_d = 0, flat_blocks_c = 0;
@@ -197,6 +198,23 @@ static tfsph_status upload_flat_cells(tfsph_batch *b, hipStream_t st)
     return TFSPH_OK;
 }
 
+// Whether every instance can run the fused 1D step (line.hpp).
+static bool line_batch(const tfsph_batch_desc *desc)
+{
+    for (int i = 0; i < desc->n_inst; ++i)
+        if (!line_step(&desc->params[i])) return false;
+    return true;
+}
+
+// workspace of a checked batch, sized for per-particle masses (the largest layout)
+static size_t batch_planned(const tfsph_batch_desc *desc, std::vector<InstLayout> L, int dim, int prec, bool line)
+{
+    for (auto &l : L) l.mass_g = l.mass_d = true;
+    Carver cv;
+    return prec == TFSPH_F64 ? batch_bytes<double>(L, dim, cv, nullptr, desc, nullptr, line)
+                             : batch_bytes<float>(L, dim, cv, nullptr, desc, nullptr, line);
+}
+
 extern "C" tfsph_status tfsph_batch_workspace_size(const tfsph_batch_desc *desc, size_t *bytes)
 {
     std::vector<InstLayout> L;
@@ -204,10 +222,7 @@ extern "C" tfsph_status tfsph_batch_workspace_size(const tfsph_batch_desc *desc,
     tfsph_status r = check_desc(desc, L, dim, prec);
     if (r != TFSPH_OK) return r;
     if (!bytes) return fail(TFSPH_E_INVALID_ARG, "bytes is NULL");
-    for (auto &l : L) l.mass_g = l.mass_d = true;   // largest layout
-    Carver cv;
-    *bytes = prec == TFSPH_F64 ? batch_bytes<double>(L, dim, cv, nullptr, desc, nullptr)
-                               : batch_bytes<float>(L, dim, cv, nullptr, desc, nullptr);
+    *bytes = batch_planned(desc, L, dim, prec, line_batch(desc));
     return TFSPH_OK;
 }
 
@@ -238,7 +253,7 @@ static tfsph_status batch_setup(tfsph_batch *b, const tfsph_batch_desc *desc, st
     table.reserve(L.size());
     Carver cv;
     cv.base = b->ws;
-    batch_bytes<R>(L, b->dim, cv, &table, desc, packed);
+    batch_bytes<R>(L, b->dim, cv, &table, desc, packed, b->line);
     Carver head;
     head.base = b->ws;
     b->table = head.take<Inst<R>>(L.size());
@@ -330,9 +345,10 @@ extern "C" tfsph_status tfsph_batch_init(tfsph_batch **out, const tfsph_batch_de
         L[i].mass_g = packed->gas.mass != nullptr;
         L[i].mass_d = packed->dust.mass != nullptr;
     }
-    size_t need = 0;
-    r = tfsph_batch_workspace_size(desc, &need);
-    if (r != TFSPH_OK) return r;
+    // a workspace that holds only the layout of the separate launches gets those
+    bool line = line_batch(desc);
+    if (line && batch_planned(desc, L, dim, prec, true) > ws_bytes) line = false;
+    const size_t need = batch_planned(desc, L, dim, prec, line);
     if (!workspace || reinterpret_cast<uintptr_t>(workspace) % 256)
         return fail(TFSPH_E_WORKSPACE, "workspace must be non-NULL and 256-byte aligned");
     if (ws_bytes < need) return fail(TFSPH_E_WORKSPACE, "workspace has %zu bytes, needs %zu", ws_bytes, need);
@@ -341,6 +357,7 @@ extern "C" tfsph_status tfsph_batch_init(tfsph_batch **out, const tfsph_batch_de
     b->n_inst = desc->n_inst;
     b->dim = dim;
     b->prec = prec;
+    b->line = line;
     b->bound = *packed;
     b->ws = static_cast<char *>(workspace);
     b->ws_bytes = ws_bytes;
@@ -374,6 +391,29 @@ static bool same_state(const tfsph_state &a, const tfsph_state &b)
     return true;
 }
 
+// Steps of the flattened form in 1D, histograms claimed: scan, records into cell
+// ranges, fused step.
+template <typename R, int KIND>
+static tfsph_status launch_flat_line(tfsph_batch *b, int n_steps, hipStream_t st)
+{
+    auto *t = static_cast<const Inst<R> *>(b->table);
+    const FlatTable T = b->flat;
+    double per_gas = 0.0, per_dust = 0.0;
+    for (const int3 &n : b->host_small) {
+        per_gas = std::max(per_gas, double(n.x) / n.z);
+        per_dust = std::max(per_dust, double(n.y) / n.z);
+    }
+    const size_t lds = line_lds<R>(T.cells_per_block, 2, per_gas, per_dust, b->bound.dust.mass != nullptr, b->flat_blocks_c);
+    const dim3 gd(b->flat_blocks_g + b->flat_blocks_d), gc(b->flat_blocks_c), blk(kBlock);
+    for (int s = 0; s < n_steps; ++s) {
+        hipLaunchKernelGGL((k_flat_scan<R>), dim3(2 * b->n_inst), dim3(kBatchMaxBlock), 0, st, t);
+        if (gd.x) hipLaunchKernelGGL((k_flat_line_scatter<R>), gd, blk, 0, st, t, T);
+        if (gc.x) hipLaunchKernelGGL((k_flat_line_step<R, KIND>), gc, blk, lds, st, t, T, b->F, lds);
+        LAUNCH_CHECK("flat_line_step");
+    }
+    return TFSPH_OK;
+}
+
 // The flattened form: every phase of a step is one launch over all instances.  The
 // first step counts from the caller's arrays; later steps use the slots claimed by
 // the previous step's finish kernel.
@@ -387,6 +427,12 @@ static tfsph_status launch_flat_t(tfsph_batch *b, int n_steps, hipStream_t st)
     if (gc.x) hipLaunchKernelGGL((k_flat_zero<R>), gc, blk, 0, st, t, T);
     if (gd.x) hipLaunchKernelGGL((k_flat_count<R>), gd, blk, 0, st, t, T);
     LAUNCH_CHECK("flat_count");
+    if constexpr (DIM == 1) {
+        if (b->line) {
+            return b->flat_kind == kForceIsoMass ? launch_flat_line<R, kForceIsoMass>(b, n_steps, st)
+                                                 : launch_flat_line<R, kForceIsoUniform>(b, n_steps, st);
+        }
+    }
     const size_t lds = update_lds_bytes<R>(T.cells_per_block);
     for (int s = 0; s < n_steps; ++s) {
         hipLaunchKernelGGL((k_flat_scan<R>), dim3(2 * b->n_inst), dim3(kBatchMaxBlock), 0, st, t);

@@ -12,6 +12,7 @@
 #pragma once
 
 #include "binning.hpp"
+#include "line.hpp"
 #include "small.hpp"
 #include "sph.hpp"
 
@@ -368,6 +369,31 @@ k_flat_update(const Inst<R> *__restrict__ insts, FlatTable T, Flags F)
     const int c0 = e.y * T.cells_per_block;
     const int c1 = min(c0 + T.cells_per_block, I.G.ncell);
     update_block<R, DIM, true>(I.G, I.Ph, I.Sg, I.Sd, I.Pg, I.Pd, F, c0, c1, smem_raw);
+}
+
+// the 1D step of line.hpp over every instance: records into cell ranges, then one
+// launch over runs of cells, with the slot claims of the next step
+template <typename R>
+__global__ void __launch_bounds__(kBlock) k_flat_line_scatter(const Inst<R> *__restrict__ insts, FlatTable T)
+{
+    bool gas;
+    int inst;
+    const int i = flat_item(T, gas, inst);
+    const Inst<R> &I = insts[inst];
+    const Sorted<R> &S = gas ? I.Sg : I.Sd;
+    if (i < S.n) line_scatter_one(I.G, gas ? I.Pg : I.Pd, S, i);
+}
+
+template <typename R, int KIND>
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(R) == 4 ? kLineWaves : 4)))
+k_flat_line_step(const Inst<R> *__restrict__ insts, FlatTable T, Flags F, size_t lds_bytes)
+{
+    extern __shared__ unsigned char smem_raw[];
+    const int2 e = T.cells[blockIdx.x];
+    const Inst<R> &I = insts[e.x];
+    const int c0 = e.y * T.cells_per_block;
+    const int c1 = min(c0 + T.cells_per_block, I.G.ncell);
+    line_block<R, KIND>(I.G, I.Ph, I.Sg, I.Sd, I.Pg, I.Pd, F, c0, c1, lds_bytes, true, smem_raw);
 }
 
 }  // namespace tfsph

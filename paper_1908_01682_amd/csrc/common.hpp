@@ -222,6 +222,7 @@ struct Sorted {
     int *tmp_id;         // [n] ids in the same layout
     int *src;            // nullable [n]: index in the unsorted arrays of sorted particle dst
     unsigned long long *nmask;   // nullable [rows][n]: neighbour bits per window row (gas)
+    R *rec;              // nullable (1D): records on their way into cell ranges (line.hpp)
 };
 
 struct Flags {

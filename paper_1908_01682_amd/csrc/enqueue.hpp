@@ -5,6 +5,7 @@
 
 #include "binning.hpp"
 #include "host.hpp"
+#include "line.hpp"
 #include "sph.hpp"
 #include "tiles.hpp"
 
@@ -26,21 +27,24 @@ inline tfsph_status enqueue_zero_counts(int ncell, Sorted<R> &Sg, Sorted<R> &Sd,
     return TFSPH_OK;
 }
 
-// count + scan + scatter + rank/gather of both phases into the workspace:
-// counting sort of both phases into (cell, id) order.  The counts must be zero
-// on entry (enqueue_zero_counts() once, then every binning leaves them zero).
+// slot claims of both phases from the caller's arrays (the counts must be zero)
 template <typename R>
-inline tfsph_status enqueue_bin(int ng, int nd, const Geom<R> &G, const Phase<R> &Pg, const Phase<R> &Pd,
-                                Sorted<R> &Sg, Sorted<R> &Sd, int *partial, const Flags &F, hipStream_t st)
+inline tfsph_status enqueue_count(int ng, int nd, int ncell, const Phase<R> &Pg, const Phase<R> &Pd, Sorted<R> &Sg,
+                                  Sorted<R> &Sd, const Flags &F, hipStream_t st)
 {
-    const int ncell = G.ncell;
-    const int ntiles = ntiles_of(ncell);
     const int bg = blocks_for(ng), bd = blocks_for(nd);
-    if (bg + bd > 0) {
-        hipLaunchKernelGGL(k_count, dim3(bg + bd), dim3(kBlock), 0, st, Pg.cell, ng, Sg.count, Sg.slot, Pd.cell,
-                           nd, Sd.count, Sd.slot, bg, ncell, F.word);
-        LAUNCH_CHECK("count");
-    }
+    if (bg + bd == 0) return TFSPH_OK;
+    hipLaunchKernelGGL(k_count, dim3(bg + bd), dim3(kBlock), 0, st, Pg.cell, ng, Sg.count, Sg.slot, Pd.cell, nd,
+                       Sd.count, Sd.slot, bg, ncell, F.word);
+    LAUNCH_CHECK("count");
+    return TFSPH_OK;
+}
+
+// exclusive scans of both histograms into the cell offsets; the counts are zero afterwards
+template <typename R>
+inline tfsph_status enqueue_scan(int ncell, Sorted<R> &Sg, Sorted<R> &Sd, int *partial, hipStream_t st)
+{
+    const int ntiles = ntiles_of(ncell);
     hipLaunchKernelGGL(k_scan_reduce, dim3(ntiles, 2), dim3(kBlock), 0, st, Sg.count, Sd.count, ncell, partial, ntiles);
     LAUNCH_CHECK("scan_reduce");
     const int inline_prefix = ntiles <= kScanInlineTiles ? 1 : 0;
@@ -51,6 +55,51 @@ inline tfsph_status enqueue_bin(int ng, int nd, const Geom<R> &G, const Phase<R>
     hipLaunchKernelGGL(k_scan_down, dim3(ntiles, 2), dim3(kBlock), 0, st, Sg.count, Sd.count, ncell, partial, ntiles,
                        Sg.start, Sd.start, inline_prefix);
     LAUNCH_CHECK("scan_down");
+    return TFSPH_OK;
+}
+
+// One fused 1D step (line.hpp) in runs of cpb cells (0: line_cells()).  claimed: the previous step claimed this one's slots;
+// claim: so does this step for the next one.
+template <typename R>
+inline tfsph_status enqueue_line(int ng, int nd, const Geom<R> &G, const Phys<R> &Ph, const Phase<R> &Pg,
+                                 const Phase<R> &Pd, Sorted<R> &Sg, Sorted<R> &Sd, int *partial, const Flags &F, int cpb,
+                                 bool claimed, bool claim, hipStream_t st)
+{
+    tfsph_status r = TFSPH_OK;
+    if (!claimed) r = enqueue_count<R>(ng, nd, G.ncell, Pg, Pd, Sg, Sd, F, st);
+    if (r == TFSPH_OK) r = enqueue_scan<R>(G.ncell, Sg, Sd, partial, st);
+    if (r != TFSPH_OK) return r;
+    const int bg = blocks_for(ng), bd = blocks_for(nd);
+    if (bg + bd > 0) {
+        hipLaunchKernelGGL(k_line_scatter<R>, dim3(bg + bd), dim3(kBlock), 0, st, G, Pg, Sg, Pd, Sd, bg);
+        LAUNCH_CHECK("line_scatter");
+    }
+    const double per_gas = double(ng) / G.ncell, per_dust = double(nd) / G.ncell;
+    if (cpb == 0) cpb = line_cells(G.win[0], per_gas);
+    const int nblocks = (G.ncell + cpb - 1) / cpb;
+    const size_t lds = line_lds<R>(cpb, G.win[0], per_gas, per_dust, Sd.has_mass != 0, nblocks);
+    if (Sg.has_mass)
+        hipLaunchKernelGGL((k_line_step<R, kForceIsoMass>), dim3(nblocks), dim3(kBlock), lds, st, G, Ph, Sg, Sd, Pg, Pd,
+                           F, cpb, nblocks, lds, claim ? 1 : 0);
+    else
+        hipLaunchKernelGGL((k_line_step<R, kForceIsoUniform>), dim3(nblocks), dim3(kBlock), lds, st, G, Ph, Sg, Sd, Pg,
+                           Pd, F, cpb, nblocks, lds, claim ? 1 : 0);
+    LAUNCH_CHECK("line_step");
+    return TFSPH_OK;
+}
+
+// count + scan + scatter + rank/gather of both phases into the workspace:
+// counting sort of both phases into (cell, id) order.  The counts must be zero
+// on entry (enqueue_zero_counts() once, then every binning leaves them zero).
+template <typename R>
+inline tfsph_status enqueue_bin(int ng, int nd, const Geom<R> &G, const Phase<R> &Pg, const Phase<R> &Pd,
+                                Sorted<R> &Sg, Sorted<R> &Sd, int *partial, const Flags &F, hipStream_t st)
+{
+    const int ncell = G.ncell;
+    const int bg = blocks_for(ng), bd = blocks_for(nd);
+    tfsph_status r = enqueue_count<R>(ng, nd, ncell, Pg, Pd, Sg, Sd, F, st);
+    if (r == TFSPH_OK) r = enqueue_scan<R>(ncell, Sg, Sd, partial, st);
+    if (r != TFSPH_OK) return r;
     if (bg + bd > 0) {
         hipLaunchKernelGGL(k_scatter, dim3(bg + bd), dim3(kBlock), 0, st, Pg.cell, Pg.id, Sg.slot, Sg.start, ng,
                            Sg.tmp_idx, Sg.tmp_id, Pd.cell, Pd.id, Sd.slot, Sd.start, nd, Sd.tmp_idx, Sd.tmp_id, bg, ncell);

@@ -74,7 +74,15 @@ struct PhaseFlags {
     bool energy;    // energy array present
     bool prs;       // gas: force record and predictor scratch
     int mask_rows = 0;   // gas: rows of neighbour bits per particle (0: no masks)
+    bool line = false;   // 1D: records of the fused step (line.hpp)
 };
+
+// 1D problems whose step runs in the fused form when the workspace holds its records
+inline bool line_step(const tfsph_params *p)
+{
+    return p->dim == 1 && p->scheme == TFSPH_SCHEME_IDIC && window_of(p, 0) <= 2 && p->eos == TFSPH_ISOTHERMAL &&
+           p->av_alpha == 0.0 && p->av_beta == 0.0;
+}
 
 template <typename R>
 Sorted<R> carve_phase(Carver &cv, int n, int dim, int ncell, PhaseFlags f)
@@ -97,6 +105,7 @@ Sorted<R> carve_phase(Carver &cv, int n, int dim, int ncell, PhaseFlags f)
     S.slot = cv.take<int>(n);
     S.tmp_idx = cv.take<int>(n);
     S.tmp_id = cv.take<int>(n);
+    S.rec = f.line ? cv.take<R>(size_t(n) * (f.mass ? 4 : 2)) : nullptr;
     S.nmask = f.mask_rows > 0 ? cv.take<unsigned long long>(size_t(f.mask_rows) * n) : nullptr;
     return S;
 }

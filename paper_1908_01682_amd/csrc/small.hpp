@@ -86,6 +86,7 @@ __host__ __device__ inline size_t small_carve(unsigned char *base, int ng, int n
     Sd.count = Sg.count + ncell;
     Sg.start = reinterpret_cast<int *>(take(sizeof(int) * (ncell + 1)));
     Sd.start = reinterpret_cast<int *>(take(sizeof(int) * (ncell + 1)));
+    Sg.rec = Sd.rec = nullptr;
     Sg.slot = Sd.slot = Sg.src = Sd.src = Sg.tmp_idx = Sd.tmp_idx = nullptr;
     return off;
 }

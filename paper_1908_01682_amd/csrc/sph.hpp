@@ -140,7 +140,8 @@ __device__ __forceinline__ bool with_row_width(int wx, F &&f)
 // offsets oa[] in cell (cx, cy, cz).  Order: rows in the pair order of
 // for_window_pairs(), inside a row x offsets ascending, then cell order.  The
 // cell ranges of a pair of rows are loaded together before it is walked.
-template <typename R, int DIM, typename T = R, typename Fn>
+// PADDED as load_chunk(): false where the records after a range may not be written yet.
+template <typename R, int DIM, typename T = R, bool PADDED = true, typename Fn>
 __device__ __forceinline__ void for_window(const Geom<R> &G, int cx, int cy, int cz, const R oa[3],
                                            const int *__restrict__ start, const R4<R> *__restrict__ data, Fn &&fn)
 {
@@ -153,7 +154,7 @@ __device__ __forceinline__ void for_window(const Geom<R> &G, int cx, int cy, int
 #pragma unroll
                 for (int k = 0; k <= 2 * WX; ++k) {
                     const T rx0 = T(oa[0]) - T(k - WX) * T(G.delta[0]);
-                    visit_range<R, DIM, true, T>(bs[t][k], be[t][k], data, rx0, ry0[t], rz0[t], fn);
+                    visit_range<R, DIM, PADDED, T>(bs[t][k], be[t][k], data, rx0, ry0[t], rz0[t], fn);
                 }
             }
         });
@@ -177,7 +178,7 @@ __device__ __forceinline__ void for_window(const Geom<R> &G, int cx, int cy, int
             for (int dx = -wx; dx <= wx; ++dx) {
                 const int lin = wrap_once(cx + dx, G.nc[0]) + row;
                 const T rx0 = T(oa[0]) - T(dx) * T(G.delta[0]);
-                visit_range<R, DIM, true, T>(start[lin], start[lin + 1], data, rx0, ry0, rz0, fn);
+                visit_range<R, DIM, PADDED, T>(start[lin], start[lin + 1], data, rx0, ry0, rz0, fn);
             }
         }
     }
@@ -401,7 +402,7 @@ __device__ __forceinline__ R density_add(const Geom<R> &G, const R4<R> &q, R rx,
 // (gas, masks allocated) the neighbour mask rows of a are stored as well; with
 // `own` a's record is returned there (it stays in registers for the caller).
 // --------------------------------------------------------------------------
-template <typename R, int DIM>
+template <typename R, int DIM, bool PADDED = true>
 __device__ __forceinline__ R density_at(const Geom<R> &G, const Sorted<R> &S, int a, bool record = false,
                                         R4<R> *own = nullptr)
 {
@@ -418,7 +419,7 @@ __device__ __forceinline__ R density_at(const Geom<R> &G, const Sorted<R> &S, in
     if (record && S.nmask)
         for_window_recording<R, DIM>(G, cx, cy, cz, oa, S.start, S.pos, S.nmask + a, S.n, term);
     else
-        for_window<R, DIM>(G, cx, cy, cz, oa, S.start, S.pos, term);
+        for_window<R, DIM, R, PADDED>(G, cx, cy, cz, oa, S.start, S.pos, term);
     return acc * G.wnorm;
 }
 
@@ -437,12 +438,12 @@ __device__ __forceinline__ void density_finish(const Geom<R> &G, const Phys<R> &
 
 // density of particle a into S.rho[a]; with want_frc also the force-pass
 // record (ox, oy, oz, p / rho^2) and, when allocated, the neighbour masks
-template <typename R, int DIM>
+template <typename R, int DIM, bool PADDED = true>
 __device__ __forceinline__ void density_store(const Geom<R> &G, const Phys<R> &Ph, const Sorted<R> &S, int a,
                                               int want_frc)
 {
     R4<R> me;
-    const R rho = density_at<R, DIM>(G, S, a, want_frc != 0, &me);
+    const R rho = density_at<R, DIM, PADDED>(G, S, a, want_frc != 0, &me);
     density_finish<R>(G, Ph, S, a, me, rho, want_frc);
 }
 
@@ -541,7 +542,7 @@ __device__ __forceinline__ T pair_rcp(T x)
     }
 }
 
-template <typename R, int DIM, int KIND>
+template <typename R, int DIM, int KIND, bool PADDED = true>
 __device__ __forceinline__ void gas_force_at(const Geom<R> &G, const Phys<R> &Ph, const Sorted<R> &S, int a,
                                              R acc[3], R &dedt)
 {
@@ -565,7 +566,7 @@ __device__ __forceinline__ void gas_force_at(const Geom<R> &G, const Phys<R> &Ph
         if (S.nmask)
             for_neighbours<R, DIM, SS>(G, cx, cy, cz, oa, S.start, S.frc, S.nmask + a, S.n, fn);
         else
-            for_window<R, DIM, SS>(G, cx, cy, cz, oa, S.start, S.frc, fn);
+            for_window<R, DIM, SS, PADDED>(G, cx, cy, cz, oa, S.start, S.frc, fn);
     };
     // f'(q) = 3 (t1^2 - s^2) with t1 = sat(1 - r / h), s = sat(1 - r / 2h); the factor 3 (and
     // a uniform mass) multiplies the sums
@@ -650,14 +651,14 @@ __device__ __forceinline__ void gas_force_at(const Geom<R> &G, const Phys<R> &Ph
 }
 
 // gas force of particle a with the loop kind picked at run time
-template <typename R, int DIM>
+template <typename R, int DIM, bool PADDED = true>
 __device__ __forceinline__ void gas_force_any(const Geom<R> &G, const Phys<R> &Ph, const Sorted<R> &S, int a,
                                               R acc[3], R &dedt)
 {
     switch (force_kind(Ph, S)) {
-    case kForceIsoUniform: gas_force_at<R, DIM, kForceIsoUniform>(G, Ph, S, a, acc, dedt); break;
-    case kForceIsoMass: gas_force_at<R, DIM, kForceIsoMass>(G, Ph, S, a, acc, dedt); break;
-    default: gas_force_at<R, DIM, kForceGeneral>(G, Ph, S, a, acc, dedt); break;
+    case kForceIsoUniform: gas_force_at<R, DIM, kForceIsoUniform, PADDED>(G, Ph, S, a, acc, dedt); break;
+    case kForceIsoMass: gas_force_at<R, DIM, kForceIsoMass, PADDED>(G, Ph, S, a, acc, dedt); break;
+    default: gas_force_at<R, DIM, kForceGeneral, PADDED>(G, Ph, S, a, acc, dedt); break;
     }
 }
 
@@ -798,7 +799,7 @@ __device__ __forceinline__ bool solve_cell(const Phys<R> &Ph, const Sorted<R> &S
 
 // Explicit part of eq. (19) for sorted gas particle a: v~ = v + tau (A + g)
 // into the predictor scratch, e += tau de/dt into the caller's energy array.
-template <typename R, int DIM, int KIND = -1>
+template <typename R, int DIM, int KIND = -1, bool PADDED = true>
 __device__ __forceinline__ void gas_predict(const Geom<R> &G, const Phys<R> &Ph, const Sorted<R> &Sg,
                                             const Phase<R> &Pg, int a)
 {
@@ -808,9 +809,9 @@ __device__ __forceinline__ void gas_predict(const Geom<R> &G, const Phys<R> &Ph,
     for (int d = 0; d < DIM; ++d) v0[d] = Sg.vel[d][a];
     R acc[3], dedt;
     if constexpr (KIND < 0)
-        gas_force_any<R, DIM>(G, Ph, Sg, a, acc, dedt);
+        gas_force_any<R, DIM, PADDED>(G, Ph, Sg, a, acc, dedt);
     else
-        gas_force_at<R, DIM, KIND>(G, Ph, Sg, a, acc, dedt);
+        gas_force_at<R, DIM, KIND, PADDED>(G, Ph, Sg, a, acc, dedt);
 #pragma unroll
     for (int d = 0; d < DIM; ++d) Sg.vt[d][a] = v0[d] + Ph.tau * (acc[d] + Ph.g[d]);
     if (Sg.energy) Pg.energy[a] = Sg.energy[a] + Ph.tau * dedt;

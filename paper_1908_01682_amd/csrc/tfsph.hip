@@ -229,6 +229,7 @@ struct tfsph_ctx {
     size_t ws_bytes;
     hipStream_t last_stream;
     int cells_per_block;
+    bool cells_set = false;     // cells_per_block was chosen by the caller
 };
 
 // record one event of a (start, stop) pair for kernel kind k when profiling
@@ -253,10 +254,26 @@ static tfsph_status timer_mark(tfsph_ctx *c, int k, hipStream_t st)
 
 static PhaseFlags gas_flags(const tfsph_params *p, bool mass_array)
 {
-    return PhaseFlags{mass_array, p->eos == TFSPH_ADIABATIC, true, mask_rows_of(p)};
+    return PhaseFlags{mass_array, p->eos == TFSPH_ADIABATIC, true, mask_rows_of(p), line_step(p)};
 }
 
-static PhaseFlags dust_flags(bool mass_array) { return PhaseFlags{mass_array, false, false}; }
+static PhaseFlags dust_flags(const tfsph_params *p, bool mass_array)
+{
+    return PhaseFlags{mass_array, false, false, 0, line_step(p)};
+}
+
+static size_t planned(const tfsph_params *p, int n_gas, int n_dust, PhaseFlags fg, PhaseFlags fd)
+{
+    return p->precision == TFSPH_F64 ? plan_bytes<double>(p, n_gas, n_dust, fg, fd)
+                                     : plan_bytes<float>(p, n_gas, n_dust, fg, fd);
+}
+
+// Without the records of the fused 1D step where `bytes` of workspace hold only the
+// layout of the separate launches.
+static void fit_flags(const tfsph_params *p, int n_gas, int n_dust, size_t bytes, PhaseFlags &fg, PhaseFlags &fd)
+{
+    if (planned(p, n_gas, n_dust, fg, fd) > bytes) fg.line = fd.line = false;
+}
 
 extern "C" tfsph_status tfsph_workspace_size(const tfsph_params *p, int64_t n_gas, int64_t n_dust, size_t *bytes)
 {
@@ -266,9 +283,8 @@ extern "C" tfsph_status tfsph_workspace_size(const tfsph_params *p, int64_t n_ga
     if (n_gas < 0 || n_dust < 0 || n_gas > 0x7fffffffLL || n_dust > 0x7fffffffLL)
         return fail(TFSPH_E_INVALID_ARG, "particle counts must be in [0, 2^31)");
     // sized for per-particle masses on both phases (the largest layout)
-    PhaseFlags fg = gas_flags(p, true), fd = dust_flags(true);
-    *bytes = p->precision == TFSPH_F64 ? plan_bytes<double>(p, (int)n_gas, (int)n_dust, fg, fd)
-                                       : plan_bytes<float>(p, (int)n_gas, (int)n_dust, fg, fd);
+    PhaseFlags fg = gas_flags(p, true), fd = dust_flags(p, true);
+    *bytes = planned(p, (int)n_gas, (int)n_dust, fg, fd);
     return TFSPH_OK;
 }
 
@@ -327,8 +343,9 @@ tfsph_status check_state_matches(const tfsph_ctx *c, const tfsph_state *s)
     return check_phase(s->dust, c->p.dim, false, false, "dust");
 }
 
+// follows / more: the previous / next step of the same call runs on st directly before / after
 template <typename R, int DIM>
-tfsph_status enqueue_step(tfsph_ctx *c, tfsph_state *s, hipStream_t st)
+tfsph_status enqueue_step(tfsph_ctx *c, tfsph_state *s, hipStream_t st, bool follows, bool more)
 {
     const Geom<R> G = make_geom<R>(&c->p);
     const Phys<R> Ph = make_phys<R>(&c->p);
@@ -338,6 +355,12 @@ tfsph_status enqueue_step(tfsph_ctx *c, tfsph_state *s, hipStream_t st)
     Flags F;
     carve_all<R>(c, Sg, Sd, partial, F);
     if (c->variant != TFSPH_VARIANT_AUTO) Sg.nmask = nullptr;    // scan the whole window in both passes
+    if constexpr (DIM == 1) {
+        // timed steps keep the separate launches, whose kinds the timers tell apart
+        if (Sg.rec && Sd.rec && c->variant == TFSPH_VARIANT_AUTO && !c->profiling)
+            return enqueue_line<R>(c->ng, c->nd, G, Ph, Pg, Pd, Sg, Sd, partial, F,
+                                   c->cells_set ? c->cells_per_block : 0, follows, more, st);
+    }
     MARK(TFSPH_KERNEL_BIN);
     tfsph_status r = enqueue_bin<R>(c->ng, c->nd, G, Pg, Pd, Sg, Sd, partial, F, st);
     if (r != TFSPH_OK) return r;
@@ -653,10 +676,11 @@ tfsph_status enqueue_density(tfsph_ctx *c, tfsph_state *s, int phase, hipStream_
     return TFSPH_OK;
 }
 
-// follows: the previous step of the same call was enqueued just before on st
+// step i of the n of one call, enqueued one after the other on st
 template <typename R>
-tfsph_status dispatch_step(tfsph_ctx *c, tfsph_state *s, hipStream_t st, bool follows = false)
+tfsph_status dispatch_step(tfsph_ctx *c, tfsph_state *s, hipStream_t st, int i_step, int n_steps)
 {
+    const bool follows = i_step > 0, more = i_step + 1 < n_steps;
     const bool imex = c->p.scheme == TFSPH_SCHEME_IMEX2;
     if (c->profiling) {
         const long long i = c->prof_steps++;
@@ -671,9 +695,9 @@ tfsph_status dispatch_step(tfsph_ctx *c, tfsph_state *s, hipStream_t st, bool fo
         }
     }
     switch (c->p.dim) {
-    case 1: return imex ? enqueue_step_imex<R, 1>(c, s, st, follows) : enqueue_step<R, 1>(c, s, st);
-    case 2: return imex ? enqueue_step_imex<R, 2>(c, s, st, follows) : enqueue_step<R, 2>(c, s, st);
-    default: return imex ? enqueue_step_imex<R, 3>(c, s, st, follows) : enqueue_step<R, 3>(c, s, st);
+    case 1: return imex ? enqueue_step_imex<R, 1>(c, s, st, follows) : enqueue_step<R, 1>(c, s, st, follows, more);
+    case 2: return imex ? enqueue_step_imex<R, 2>(c, s, st, follows) : enqueue_step<R, 2>(c, s, st, follows, more);
+    default: return imex ? enqueue_step_imex<R, 3>(c, s, st, follows) : enqueue_step<R, 3>(c, s, st, follows, more);
     }
 }
 
@@ -727,9 +751,10 @@ extern "C" tfsph_status tfsph_init(tfsph_ctx **out, const tfsph_params *p, tfsph
     if (r != TFSPH_OK) return r;
     r = check_phase(s->dust, p->dim, false, false, "dust");
     if (r != TFSPH_OK) return r;
-    size_t need = 0;
-    r = tfsph_workspace_size(p, s->gas.n, s->dust.n, &need);
-    if (r != TFSPH_OK) return r;
+    // sized, as tfsph_workspace_size() is, for per-particle masses on both phases
+    PhaseFlags fg = gas_flags(p, true), fd = dust_flags(p, true);
+    fit_flags(p, (int)s->gas.n, (int)s->dust.n, ws_bytes, fg, fd);
+    const size_t need = planned(p, (int)s->gas.n, (int)s->dust.n, fg, fd);
     if (!workspace) return fail(TFSPH_E_WORKSPACE, "workspace is NULL");
     if (reinterpret_cast<uintptr_t>(workspace) % 256) return fail(TFSPH_E_WORKSPACE, "workspace must be 256-byte aligned");
     if (ws_bytes < need) return fail(TFSPH_E_WORKSPACE, "workspace has %zu bytes, needs %zu", ws_bytes, need);
@@ -738,8 +763,10 @@ extern "C" tfsph_status tfsph_init(tfsph_ctx **out, const tfsph_params *p, tfsph
     c->p = *p;
     c->ng = (int)s->gas.n;
     c->nd = (int)s->dust.n;
-    c->fg = gas_flags(p, s->gas.mass != nullptr);
-    c->fd = dust_flags(s->dust.mass != nullptr);
+    c->fg = fg;
+    c->fd = fd;
+    c->fg.mass = s->gas.mass != nullptr;
+    c->fd.mass = s->dust.mass != nullptr;
     c->mg_uniform = s->gas.mass_uniform;
     c->md_uniform = s->dust.mass_uniform;
     c->ws = static_cast<char *>(workspace);
@@ -767,7 +794,7 @@ extern "C" tfsph_status tfsph_step(tfsph_ctx *c, tfsph_state *s, int32_t n_steps
     r = try_small_steps(c, s, n_steps, st, done);
     if (r != TFSPH_OK || done) return r;
     for (int i = 0; i < n_steps; ++i) {
-        r = c->p.precision == TFSPH_F64 ? dispatch_step<double>(c, s, st, i > 0) : dispatch_step<float>(c, s, st, i > 0);
+        r = c->p.precision == TFSPH_F64 ? dispatch_step<double>(c, s, st, i, n_steps) : dispatch_step<float>(c, s, st, i, n_steps);
         if (r != TFSPH_OK) return r;
     }
     return TFSPH_OK;
@@ -846,6 +873,7 @@ extern "C" tfsph_status tfsph_set_cells_per_block(tfsph_ctx *c, int32_t cells)
     if (cells < 1 || cells > kMaxCellsPerBlock)
         return fail(TFSPH_E_INVALID_ARG, "cells per block %d outside [1, %d]", cells, kMaxCellsPerBlock);
     c->cells_per_block = cells;
+    c->cells_set = true;
     drop_graph(c->sg);
     return TFSPH_OK;
 }
@@ -948,8 +976,8 @@ extern "C" tfsph_status tfsph_step_graph(tfsph_ctx *c, tfsph_state *s, int32_t n
             c->profiling = false;
             HIP_TRY(hipStreamBeginCapture(c->capture_stream, hipStreamCaptureModeThreadLocal));
             for (int i = 0; i < chunk && r == TFSPH_OK; ++i)
-                r = c->p.precision == TFSPH_F64 ? dispatch_step<double>(c, s, c->capture_stream, i > 0)
-                                                : dispatch_step<float>(c, s, c->capture_stream, i > 0);
+                r = c->p.precision == TFSPH_F64 ? dispatch_step<double>(c, s, c->capture_stream, i, chunk)
+                                                : dispatch_step<float>(c, s, c->capture_stream, i, chunk);
             hipGraph_t g = nullptr;
             hipError_t e = hipStreamEndCapture(c->capture_stream, &g);
             c->profiling = prof;
@@ -965,7 +993,7 @@ extern "C" tfsph_status tfsph_step_graph(tfsph_ctx *c, tfsph_state *s, int32_t n
         for (int k = 0; k < n_full; ++k) HIP_TRY(hipGraphLaunch(c->sg.exec, st));
     }
     for (int i = 0; i < rem; ++i) {
-        r = c->p.precision == TFSPH_F64 ? dispatch_step<double>(c, s, st, i > 0) : dispatch_step<float>(c, s, st, i > 0);
+        r = c->p.precision == TFSPH_F64 ? dispatch_step<double>(c, s, st, i, rem) : dispatch_step<float>(c, s, st, i, rem);
         if (r != TFSPH_OK) return r;
     }
     return TFSPH_OK;
@@ -1027,9 +1055,9 @@ extern "C" tfsph_status tfsph_step_noalloc(const tfsph_params *p, tfsph_state *s
     if (r != TFSPH_OK) return r;
     r = check_phase(s->dust, p->dim, false, false, "dust");
     if (r != TFSPH_OK) return r;
-    const PhaseFlags fg = gas_flags(p, s->gas.mass != nullptr), fd = dust_flags(s->dust.mass != nullptr);
-    const size_t need = p->precision == TFSPH_F64 ? plan_bytes<double>(p, (int)s->gas.n, (int)s->dust.n, fg, fd)
-                                                  : plan_bytes<float>(p, (int)s->gas.n, (int)s->dust.n, fg, fd);
+    PhaseFlags fg = gas_flags(p, s->gas.mass != nullptr), fd = dust_flags(p, s->dust.mass != nullptr);
+    fit_flags(p, (int)s->gas.n, (int)s->dust.n, kScratchBytes, fg, fd);
+    const size_t need = planned(p, (int)s->gas.n, (int)s->dust.n, fg, fd);
     if (need > kScratchBytes)
         return fail(TFSPH_E_WORKSPACE, "the problem needs %zu bytes of workspace; the library's static scratch holds %zu",
                     need, kScratchBytes);
@@ -1056,7 +1084,7 @@ extern "C" tfsph_status tfsph_step_noalloc(const tfsph_params *p, tfsph_state *s
     r = try_small_steps(&c, s, n_steps, st, done);
     if (r != TFSPH_OK) return r;
     for (int i = 0; i < n_steps && !done; ++i) {
-        r = p->precision == TFSPH_F64 ? dispatch_step<double>(&c, s, st, i > 0) : dispatch_step<float>(&c, s, st, i > 0);
+        r = p->precision == TFSPH_F64 ? dispatch_step<double>(&c, s, st, i, n_steps) : dispatch_step<float>(&c, s, st, i, n_steps);
         if (r != TFSPH_OK) return r;
     }
     if (flags_out || one_phase_out) {
