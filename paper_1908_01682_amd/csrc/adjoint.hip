@@ -146,16 +146,15 @@ tfsph_status fill_dev(T *out, T v, int n, hipStream_t st)
         if (r_ != TFSPH_OK) return r_;      \
     } while (0)
 
+// both phases of a state in one launch
 template <typename R>
-tfsph_status copy_state(const Phase<R> &in, const Phase<R> &out, int dim, hipStream_t st)
+tfsph_status copy_state(const Phase<R> &in_g, const Phase<R> &out_g, const Phase<R> &in_d, const Phase<R> &out_d, int dim,
+                        hipStream_t st)
 {
-    TRY(copy_dev<int>(in.cell, out.cell, in.n, st));
-    TRY(copy_dev<int>(in.id, out.id, in.n, st));
-    for (int k = 0; k < dim; ++k) {
-        TRY(copy_dev<R>(in.off[k], out.off[k], in.n, st));
-        TRY(copy_dev<R>(in.vel[k], out.vel[k], in.n, st));
-    }
-    if (in.mass && out.mass) TRY(copy_dev<R>(in.mass, const_cast<R *>(out.mass), in.n, st));
+    const int bg = blocks_for(in_g.n), bd = blocks_for(in_d.n);
+    if (bg + bd == 0) return TFSPH_OK;
+    hipLaunchKernelGGL(k_copy_state<R>, dim3(bg + bd), dim3(kBlock), 0, st, in_g, out_g, in_d, out_d, dim, bg);
+    LAUNCH_CHECK("copy_state");
     return TFSPH_OK;
 }
 
@@ -237,14 +236,12 @@ tfsph_status run_adjoint(const tfsph_params *p, const tfsph_state *s, int n_step
     TRY(fill_dev<double>(L.acc, 0.0, 4, st));
     for (int t = 0; t <= K; ++t) TRY(enqueue_zero_counts<R>(G.ncell, L.tg[t], L.td[t], st));
     // forward sweep with checkpoints
-    TRY(copy_state<R>(Ig, L.W.g, DIM, st));
-    TRY(copy_state<R>(Id, L.W.d, DIM, st));
+    TRY(copy_state<R>(Ig, L.W.g, Id, L.W.d, DIM, st));
     // (the last segment's steps keep their tapes, so that segment is not replayed)
     const int last_first = (nseg - 1) * K;
     for (int i = 0; i < n_steps; ++i) {
         if (i % K == 0) {
-            TRY(copy_state<R>(L.W.g, L.ckpt[i / K].g, DIM, st));
-            TRY(copy_state<R>(L.W.d, L.ckpt[i / K].d, DIM, st));
+            TRY(copy_state<R>(L.W.g, L.ckpt[i / K].g, L.W.d, L.ckpt[i / K].d, DIM, st));
         }
         TRY((fwd_step<R, DIM>(G, Ph, L, i >= last_first ? i - last_first : 0, st)));
     }
@@ -274,8 +271,7 @@ tfsph_status run_adjoint(const tfsph_params *p, const tfsph_state *s, int n_step
     for (int seg = nseg - 1; seg >= 0; --seg) {
         const int first = seg * K, len = std::min(K, n_steps - first);
         if (seg < nseg - 1) {
-            TRY(copy_state<R>(L.ckpt[seg].g, L.W.g, DIM, st));
-            TRY(copy_state<R>(L.ckpt[seg].d, L.W.d, DIM, st));
+            TRY(copy_state<R>(L.ckpt[seg].g, L.W.g, L.ckpt[seg].d, L.W.d, DIM, st));
             for (int t = 0; t < len; ++t) TRY((fwd_step<R, DIM>(G, Ph, L, t, st)));
         }
         for (int t = len - 1; t >= 0; --t) TRY((rev_step<R, DIM>(G, Ph, L, t, first + t, st)));

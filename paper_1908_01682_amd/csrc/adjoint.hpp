@@ -81,7 +81,8 @@ k_adj_cell(Geom<R> G, Phys<R> Ph, Sorted<R> Sg, Sorted<R> Sd, AdjPhase<R> outg, 
     __shared__ double red[kBlock];
     R *abar[3] = {abar0, abar1, abar2};
     const R tau = Ph.tau;
-    const int c0 = blockIdx.x * cells_per_block;
+    const int blk = xcd_block(gridDim.x);
+    const int c0 = blk * cells_per_block;
     const int c1 = min(c0 + cells_per_block, G.ncell);
     const int ga = Sg.start[c0], gb = Sg.start[c1];
     const int da = Sd.start[c0], db = Sd.start[c1];
@@ -227,7 +228,7 @@ k_adj_cell(Geom<R> G, Phys<R> Ph, Sorted<R> Sg, Sorted<R> Sd, AdjPhase<R> outg, 
         if (threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
         __syncthreads();
     }
-    if (threadIdx.x == 0) sbar_part[blockIdx.x] = red[0];
+    if (threadIdx.x == 0) sbar_part[blk] = red[0];
 }
 
 // ---------------------------------------------------------------------------
@@ -238,7 +239,7 @@ __global__ void __launch_bounds__(kBlock)
 k_adj_force(Geom<R> G, Phys<R> Ph, Sorted<R> Sg, const R *abar0, const R *abar1, const R *abar2,
             AdjPhase<R> outg /* x: xbar of the step output (sorted) */, R *xacc0, R *xacc1, R *xacc2, R *rhobar)
 {
-    const int a = blockIdx.x * kBlock + threadIdx.x;
+    const int a = xcd_block(gridDim.x) * kBlock + threadIdx.x;
     if (a >= Sg.n) return;
     const R *abar[3] = {abar0, abar1, abar2};
     R *xacc[3] = {xacc0, xacc1, xacc2};
@@ -292,7 +293,7 @@ template <typename R, int DIM>
 __global__ void __launch_bounds__(kBlock)
 k_adj_density(Geom<R> G, Sorted<R> S, const R *rhobar, R *xacc0, R *xacc1, R *xacc2)
 {
-    const int a = blockIdx.x * kBlock + threadIdx.x;
+    const int a = xcd_block(gridDim.x) * kBlock + threadIdx.x;
     if (a >= S.n) return;
     R *xacc[3] = {xacc0, xacc1, xacc2};
     int cx, cy, cz;
@@ -435,6 +436,26 @@ __global__ void __launch_bounds__(kBlock) k_copy(const T *in, T *out, int n)
 {
     const int i = blockIdx.x * kBlock + threadIdx.x;
     if (i < n) out[i] = in[i];
+}
+
+// Both phases of a state copied in one launch (blocks below blocks_g are gas); the mass
+// only where both have it.  A checkpoint of the 512^2 2D wave was 12 launches of 2.6 us; 7 us now.
+template <typename R>
+__global__ void __launch_bounds__(kBlock)
+k_copy_state(Phase<R> in_g, Phase<R> out_g, Phase<R> in_d, Phase<R> out_d, int dim, int blocks_g)
+{
+    const bool gas = int(blockIdx.x) < blocks_g;
+    const int i = (gas ? blockIdx.x : blockIdx.x - blocks_g) * kBlock + threadIdx.x;
+    const Phase<R> &in = gas ? in_g : in_d;
+    const Phase<R> &out = gas ? out_g : out_d;
+    if (i >= in.n) return;
+    out.cell[i] = in.cell[i];
+    out.id[i] = in.id[i];
+    for (int k = 0; k < dim; ++k) {
+        out.off[k][i] = in.off[k][i];
+        out.vel[k][i] = in.vel[k][i];
+    }
+    if (in.mass && out.mass) const_cast<R *>(out.mass)[i] = in.mass[i];
 }
 
 template <typename T>
