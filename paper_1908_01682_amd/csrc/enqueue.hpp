@@ -40,10 +40,20 @@ inline tfsph_status enqueue_count(int ng, int nd, int ncell, const Phase<R> &Pg,
     return TFSPH_OK;
 }
 
+// whether the scan of a grid leaves the counts for the scatter to clear (k_scan_one)
+inline bool scan_keeps_counts(int ncell) { return ncell <= kScanOneCells; }
+
 // exclusive scans of both histograms into the cell offsets; the counts are zero afterwards
+// or, with scan_keeps_counts(), untouched
 template <typename R>
 inline tfsph_status enqueue_scan(int ncell, Sorted<R> &Sg, Sorted<R> &Sd, int *partial, hipStream_t st)
 {
+    if (scan_keeps_counts(ncell)) {
+        hipLaunchKernelGGL(k_scan_one, dim3((ncell + kScanOneTile - 1) / kScanOneTile, 2), dim3(kScanOneThreads), 0, st,
+                           Sg.count, Sd.count, ncell, Sg.start, Sd.start);
+        LAUNCH_CHECK("scan_one");
+        return TFSPH_OK;
+    }
     const int ntiles = ntiles_of(ncell);
     hipLaunchKernelGGL(k_scan_reduce, dim3(ntiles, 2), dim3(kBlock), 0, st, Sg.count, Sd.count, ncell, partial, ntiles);
     LAUNCH_CHECK("scan_reduce");
@@ -71,7 +81,8 @@ inline tfsph_status enqueue_line(int ng, int nd, const Geom<R> &G, const Phys<R>
     if (r != TFSPH_OK) return r;
     const int bg = blocks_for(ng), bd = blocks_for(nd);
     if (bg + bd > 0) {
-        hipLaunchKernelGGL(k_line_scatter<R>, dim3(bg + bd), dim3(kBlock), 0, st, G, Pg, Sg, Pd, Sd, bg);
+        hipLaunchKernelGGL(k_line_scatter<R>, dim3(bg + bd), dim3(kBlock), 0, st, G, Pg, Sg, Pd, Sd, bg,
+                           scan_keeps_counts(G.ncell) ? 1 : 0);
         LAUNCH_CHECK("line_scatter");
     }
     const double per_gas = double(ng) / G.ncell, per_dust = double(nd) / G.ncell;
@@ -102,7 +113,8 @@ inline tfsph_status enqueue_bin(int ng, int nd, const Geom<R> &G, const Phase<R>
     if (r != TFSPH_OK) return r;
     if (bg + bd > 0) {
         hipLaunchKernelGGL(k_scatter, dim3(bg + bd), dim3(kBlock), 0, st, Pg.cell, Pg.id, Sg.slot, Sg.start, ng,
-                           Sg.tmp_idx, Sg.tmp_id, Pd.cell, Pd.id, Sd.slot, Sd.start, nd, Sd.tmp_idx, Sd.tmp_id, bg, ncell);
+                           Sg.tmp_idx, Sg.tmp_id, Pd.cell, Pd.id, Sd.slot, Sd.start, nd, Sd.tmp_idx, Sd.tmp_id, bg, ncell,
+                           scan_keeps_counts(ncell) ? Sg.count : nullptr, Sd.count);
         LAUNCH_CHECK("scatter");
         hipLaunchKernelGGL(k_rank_gather<R>, dim3(bg + bd), dim3(kBlock), 0, st, G, Pg, Sg, Pd, Sd, bg, F.word);
         LAUNCH_CHECK("rank_gather");

@@ -62,8 +62,9 @@ __device__ __forceinline__ R4<R> line_record(const Phase<R> &P, const Sorted<R> 
 
 template <typename R>
 __global__ void __launch_bounds__(kBlock)
-k_line_scatter(Geom<R> G, Phase<R> Pg, Sorted<R> Sg, Phase<R> Pd, Sorted<R> Sd, int blocks_g)
+k_line_scatter(Geom<R> G, Phase<R> Pg, Sorted<R> Sg, Phase<R> Pd, Sorted<R> Sd, int blocks_g, int clear)
 {
+    clear_counts(clear ? Sg.count : nullptr, Sd.count, G.ncell);
     const bool gas = int(blockIdx.x) < blocks_g;
     const int i = (gas ? blockIdx.x : blockIdx.x - blocks_g) * kBlock + threadIdx.x;
     if (gas) {
