@@ -245,7 +245,7 @@ tfsph_status tfsph_step_graph(tfsph_ctx *ctx, tfsph_state *s, int32_t n_steps, i
 /* ---------------------------------------------------------------------------
  * Batched form: many independent problems (instances) with their own
  * parameters, advanced together, either by one persistent kernel launch per
- * call or by six launches per step over every instance (the form is chosen
+ * call or by a few launches per step over every instance (the form is chosen
  * with tfsph_batch_tuning, below).  The packed state holds every instance's particles back to back: instance i
  * owns gas particles [gas_offset[i], gas_offset[i+1]) and dust particles
  * [dust_offset[i], dust_offset[i+1]) of the packed arrays; its cell indices
@@ -269,12 +269,15 @@ typedef struct {
 
 /* Forms of the batched step (results are bitwise the same):
  *  - TFSPH_BATCH_PERSISTENT: one persistent launch per call, one workgroup per
- *    instance for all its steps (no workgroup waits on another); the launch
- *    lasts as long as the largest instance takes on one compute unit.
+ *    instance for all its steps (no workgroup waits on another), in LDS where the
+ *    instance fits it; the launch lasts as long as the largest instance takes on
+ *    one compute unit.
  *  - TFSPH_BATCH_FLAT: each phase of a step (scan, scatter, rank + gather,
  *    density, force + predictor, cell sums + solve + update) is one launch over
  *    every instance, with blocks dealt out per instance (a block never
- *    straddles two); six launches per step, best replayed as a hipGraph. */
+ *    straddles two); six launches per step, three for 1D instances without
+ *    viscosity (scan, records into cell ranges, one fused step), best replayed as
+ *    a hipGraph. */
 enum { TFSPH_BATCH_PERSISTENT = 0, TFSPH_BATCH_FLAT = 1 };
 
 typedef struct {
@@ -301,7 +304,7 @@ tfsph_status tfsph_batch_init(tfsph_batch **out, const tfsph_batch_desc *desc, t
 tfsph_status tfsph_batch_set_tuning(tfsph_batch *b, const tfsph_batch_tuning *tuning);
 
 /* Advance every instance n_steps IDIC steps: one kernel launch (persistent
- * form) or six launches per step (flattened form).  The packed state must be
+ * form) or the launches of the flattened form per step.  The packed state must be
  * the one bound at init (TFSPH_E_STATE otherwise). */
 tfsph_status tfsph_step_batched(tfsph_batch *b, tfsph_state *packed, int32_t n_steps, void *hip_stream);
 
@@ -349,15 +352,19 @@ tfsph_status tfsph_step_adjoint(const tfsph_params *p, const tfsph_state *initia
 
 /* Pair-loop implementation of a context's steps.
  *  - TFSPH_VARIANT_AUTO (the default): the density pass scans the neighbour
- *    window in global memory and records, per gas particle and window row, a
- *    64-bit mask of the candidates inside the support (rows of at most 64
- *    candidates, windows of at most 5 cells along x); the force pass visits
- *    only those and scans the rest.  The masks take 8 bytes per gas particle
+ *    window in global memory (3D windows of one cell: tests it on the matrix
+ *    cores) and records, per gas particle and pair of window rows, a 64-bit mask
+ *    of the candidates inside the support (pairs of at most 64 candidates, windows
+ *    of at most 5 cells along x); the force pass visits only those and scans the
+ *    rest.  Small 1D and 2D problems run whole calls in one workgroup with their
+ *    working set in LDS, and larger 1D isothermal ones in a fused step; steps
+ *    timed with tfsph_profile() keep the separate launches.  The masks take 8 bytes per gas particle
  *    and row of the window in the workspace (tfsph_workspace_size).
- *  - TFSPH_VARIANT_GLOBAL: both passes scan the whole window in global memory.
+ *  - TFSPH_VARIANT_GLOBAL: both passes scan the whole window in global memory, in
+ *    separate launches.
  *  - TFSPH_VARIANT_LDS_BRICKS: not built (TFSPH_E_UNSUPPORTED): blocks of
  *    cells staged in LDS were slower than the global loops.
- * Both variants visit neighbours in the same order with the same arithmetic,
+ * Every form visits neighbours in the same order with the same arithmetic,
  * and terms outside the support are exactly zero, so results are bitwise
  * equal.  Selecting a variant drops the context's cached step graph.  Returns
  * TFSPH_E_INVALID_ARG for an unknown variant or a null context. */

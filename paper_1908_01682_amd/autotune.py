@@ -1,8 +1,8 @@
 """Launch-shape autotuners.
 
 Batched step (``tune``): the candidates are the persistent form (one workgroup per
-instance) at several workgroup sizes and the flattened form (six launches per step over
-every instance) at several cells per workgroup of its update launch.  For a batch signature (device name, dim, precision, instance count,
+instance) at several workgroup sizes and the flattened form (launches per step over every
+instance) at several cells per workgroup of its update launch.  For a batch signature (device name, dim, precision, instance count,
 size distribution) it times every candidate on the real batch.
 
 Plain step (``tune_plain``): the candidates are the cells owned by one block of the

@@ -83,12 +83,13 @@ def _run(prob, precision, variant, cpb):
     return out
 
 
-@pytest.mark.parametrize("cpb", [0, 7, 256])
+# the default run length covers the large grid
+RUNS = [(name, cpb) for name in sorted(CASES) for cpb in ((0,) if name == "wave_many_runs" else (0, 7, 256))]
+
+
 @pytest.mark.parametrize("precision", [0, 1])
-@pytest.mark.parametrize("name", sorted(CASES))
+@pytest.mark.parametrize("name,cpb", RUNS)
 def test_fused_step_equals_separate_launches_bitwise(name, precision, cpb):
-    if cpb and name == "wave_many_runs":
-        pytest.skip("the default run length covers the large grid")
     prob = CASES[name]()
     banner(f"line {name} n=({prob.gas.n},{prob.dust.n}) precision {precision} cells per block {cpb}")
     assert _run(prob, precision, T.TFSPH_VARIANT_AUTO, cpb) == _run(prob, precision, T.TFSPH_VARIANT_GLOBAL, cpb)
