@@ -354,4 +354,15 @@ inline bool tile_windows(const Geom<R> &G, int n)
     return true;
 }
 
+// Whether the density pass of n particles takes the tile kernel.  Its FP32 form holds 4
+// waves per SIMD against 7 of the scan: with 4097 to 7168 waves (1024 SIMDs) it takes
+// two rounds where the scan takes one.  IDIC step, us, tiles / scan: 72^3 particles
+// (5832 waves) 184 / 178; 64^3 (4096) 134 / 135; 80^3 (8000) 223 / 241.
+template <typename R>
+inline bool tile_density(const Geom<R> &G, int n)
+{
+    const int waves = n / 64 + (n % 64 != 0);
+    return tile_windows(G, n) && !(sizeof(R) == 4 && waves > 4 * 1024 && waves <= 7 * 1024);
+}
+
 }  // namespace tfsph
