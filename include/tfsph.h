@@ -239,7 +239,8 @@ tfsph_status tfsph_cfl_dt(const tfsph_params *p, double signal_speed, double *dt
  * no memset nodes) and the graph is replayed on hip_stream; n_steps need not
  * be a multiple of chunk (the remainder runs eagerly).  Results are bitwise
  * those of tfsph_step.  The graph is tied to the state's array addresses:
- * a state with other addresses is captured anew.  chunk in 1..256. */
+ * a state with other addresses is captured anew.  chunk in 1..256.  (A problem
+ * small enough to run whole calls in one workgroup is launched directly.) */
 tfsph_status tfsph_step_graph(tfsph_ctx *ctx, tfsph_state *s, int32_t n_steps, int32_t chunk, void *hip_stream);
 
 /* ---------------------------------------------------------------------------
