@@ -285,8 +285,9 @@ typedef struct {
     int32_t block;                  /* persistent form: threads per workgroup, multiple of 64 in
                                        64..1024 (0 = 512); the flattened form uses 256 */
     int32_t form;                   /* TFSPH_BATCH_PERSISTENT (0) or TFSPH_BATCH_FLAT */
-    int32_t cells_per_block;        /* flattened form: cells per workgroup of its update launch,
-                                       1..256 (0 = the single-problem default for the dimension) */
+    int32_t cells_per_block;        /* flattened form: cells per workgroup of its update launch (in
+                                       the fused 1D step on average), 1..256 (0 = the
+                                       single-problem default for the dimension) */
 } tfsph_batch_tuning;
 
 /* Host-only: workspace bytes for a batch (256-byte aligned buffer). */
@@ -358,8 +359,8 @@ tfsph_status tfsph_step_adjoint(const tfsph_params *p, const tfsph_state *initia
  *    of the candidates inside the support (pairs of at most 64 candidates, windows
  *    of at most 5 cells along x); the force pass visits only those and scans the
  *    rest.  Small 1D and 2D problems run whole calls in one workgroup with their
- *    working set in LDS, and larger 1D isothermal ones in a fused step; steps
- *    timed with tfsph_profile() keep the separate launches.  The masks take 8 bytes per gas particle
+ *    working set in LDS, and larger 1D isothermal ones with up to four gas
+ *    particles per cell on average in a fused step; steps timed with tfsph_profile() keep the separate launches.  The masks take 8 bytes per gas particle
  *    and row of the window in the workspace (tfsph_workspace_size).
  *  - TFSPH_VARIANT_GLOBAL: both passes scan the whole window in global memory, in
  *    separate launches.
@@ -439,7 +440,7 @@ tfsph_status tfsph_cells_to_positions(const tfsph_params *p, int64_t n, const in
 tfsph_status tfsph_step_noalloc(const tfsph_params *p, tfsph_state *s, int32_t n_steps, uint32_t *flags_out,
                                 int64_t *one_phase_out, void *hip_stream);
 
-/* Release the context (host memory only; the workspace stays the caller's). *//* Release the context (host memory only; the workspace stays the caller's). */
+/* Release the context (host memory only; the workspace stays the caller's). */
 tfsph_status tfsph_destroy(tfsph_ctx *ctx);
 
 #ifdef __cplusplus

@@ -391,19 +391,27 @@ static bool same_state(const tfsph_state &a, const tfsph_state &b)
     return true;
 }
 
+// LDS of the fused step of a 1D batch, 0 where the average runs of some instance do not fit.
+template <typename R>
+static size_t flat_line_lds(const tfsph_batch *b)
+{
+    size_t most = 0;
+    for (const int3 &n : b->host_small) {
+        const size_t lds = line_lds<R>(n.x, n.y, n.z, 2, (n.z + b->flat_cpb - 1) / b->flat_cpb, b->flat_blocks_c,
+                                         b->bound.dust.mass != nullptr);
+        if (lds == 0) return 0;
+        most = std::max(most, lds);
+    }
+    return most;
+}
+
 // Steps of the flattened form in 1D, histograms claimed: scan, records into cell
 // ranges, fused step.
 template <typename R, int KIND>
-static tfsph_status launch_flat_line(tfsph_batch *b, int n_steps, hipStream_t st)
+static tfsph_status launch_flat_line(tfsph_batch *b, int n_steps, size_t lds, hipStream_t st)
 {
     auto *t = static_cast<const Inst<R> *>(b->table);
     const FlatTable T = b->flat;
-    double per_gas = 0.0, per_dust = 0.0;
-    for (const int3 &n : b->host_small) {
-        per_gas = std::max(per_gas, double(n.x) / n.z);
-        per_dust = std::max(per_dust, double(n.y) / n.z);
-    }
-    const size_t lds = line_lds<R>(T.cells_per_block, 2, per_gas, per_dust, b->bound.dust.mass != nullptr, b->flat_blocks_c);
     const dim3 gd(b->flat_blocks_g + b->flat_blocks_d), gc(b->flat_blocks_c), blk(kBlock);
     for (int s = 0; s < n_steps; ++s) {
         hipLaunchKernelGGL((k_flat_scan<R>), dim3(2 * b->n_inst), dim3(kBatchMaxBlock), 0, st, t);
@@ -428,10 +436,10 @@ static tfsph_status launch_flat_t(tfsph_batch *b, int n_steps, hipStream_t st)
     if (gd.x) hipLaunchKernelGGL((k_flat_count<R>), gd, blk, 0, st, t, T);
     LAUNCH_CHECK("flat_count");
     if constexpr (DIM == 1) {
-        if (b->line) {
-            return b->flat_kind == kForceIsoMass ? launch_flat_line<R, kForceIsoMass>(b, n_steps, st)
-                                                 : launch_flat_line<R, kForceIsoUniform>(b, n_steps, st);
-        }
+        const size_t lds = b->line ? flat_line_lds<R>(b) : 0;
+        if (lds > 0)
+            return b->flat_kind == kForceIsoMass ? launch_flat_line<R, kForceIsoMass>(b, n_steps, lds, st)
+                                                 : launch_flat_line<R, kForceIsoUniform>(b, n_steps, lds, st);
     }
     const size_t lds = update_lds_bytes<R>(T.cells_per_block);
     for (int s = 0; s < n_steps; ++s) {

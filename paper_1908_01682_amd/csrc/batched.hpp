@@ -382,18 +382,22 @@ __global__ void __launch_bounds__(kBlock) k_flat_line_scatter(const Inst<R> *__r
     const Inst<R> &I = insts[inst];
     const Sorted<R> &S = gas ? I.Sg : I.Sd;
     if (i < S.n) line_scatter_one(I.G, gas ? I.Pg : I.Pd, S, i);
+    // the blocks of one phase cut the instance's runs
+    if (gas || I.Sg.n == 0)
+        line_cut(I.G, I.Sg, I.Sd, (I.G.ncell + T.cells_per_block - 1) / T.cells_per_block, i,
+                 (S.n + kBlock - 1) / kBlock * kBlock);
 }
 
 template <typename R, int KIND>
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(R) == 4 ? kLineWaves : 4)))
 k_flat_line_step(const Inst<R> *__restrict__ insts, FlatTable T, Flags F, size_t lds_bytes)
 {
-    extern __shared__ unsigned char smem_raw[];
+    extern __shared__ __align__(16) unsigned char smem_line[];     // 16-byte records from the first byte on
     const int2 e = T.cells[blockIdx.x];
     const Inst<R> &I = insts[e.x];
-    const int c0 = e.y * T.cells_per_block;
-    const int c1 = min(c0 + T.cells_per_block, I.G.ncell);
-    line_block<R, KIND>(I.G, I.Ph, I.Sg, I.Sd, I.Pg, I.Pd, F, c0, c1, lds_bytes, true, smem_raw);
+    int c0, c1;
+    line_cells_of(I.Sg, I.Sd, e.y, c0, c1);
+    line_block<R, KIND>(I.G, I.Ph, I.Sg, I.Sd, I.Pg, I.Pd, F, c0, c1, lds_bytes, true, smem_line);
 }
 
 }  // namespace tfsph

@@ -298,6 +298,25 @@ k_scatter(const int *cell_g, const int *id_g, const int *slot_g, const int *star
 }
 
 // --- rank by id inside the cell and gather every field ---------------------------
+// Place in the cell range [b, e) of ids of the one at j, myid; ids are loaded C at a time.
+template <int C = kChunk>
+__device__ __forceinline__ int rank_in_cell(const int *ids, int b, int e, int myid, int j, unsigned int *flags)
+{
+    if (e - b > kMaxRankCell) {
+        atomicOr(flags, 8u);
+        return j;
+    }
+    int rank = 0;
+    for (int k = b; k < e; k += C) {
+        int t[C];
+#pragma unroll
+        for (int u = 0; u < C; ++u) t[u] = ids[min(k + u, e - 1)];
+#pragma unroll
+        for (int u = 0; u < C; ++u) rank += (k + u < e && t[u] < myid) ? 1 : 0;
+    }
+    return b + rank;
+}
+
 template <typename R>
 __device__ __forceinline__ void rank_gather_one(const Geom<R> &G, const Phase<R> &P, const Sorted<R> &S, int j,
                                                 unsigned int *flags)
@@ -313,22 +332,7 @@ __device__ __forceinline__ void rank_gather_one(const Geom<R> &G, const Phase<R>
     }
     const R m = P.mass ? P.mass[i] : P.m_uniform;
     const R en = S.energy ? P.energy[i] : R(0);
-    const int b = S.start[c];
-    const int e = S.start[c + 1];
-    int rank = 0;
-    if (e - b <= kMaxRankCell) {
-        for (int k = b; k < e; k += kChunk) {
-            int t[kChunk];
-#pragma unroll
-            for (int u = 0; u < kChunk; ++u) t[u] = S.tmp_id[min(k + u, e - 1)];
-#pragma unroll
-            for (int u = 0; u < kChunk; ++u) rank += (k + u < e && t[u] < myid) ? 1 : 0;
-        }
-    } else {
-        rank = j - b;
-        atomicOr(flags, 8u);
-    }
-    const int dst = b + rank;
+    const int dst = rank_in_cell(S.tmp_id, S.start[c], S.start[c + 1], myid, j, flags);
     if (S.src) S.src[dst] = i;
     S.cell[dst] = c;
     S.id[dst] = myid;

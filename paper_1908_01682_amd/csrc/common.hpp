@@ -115,6 +115,7 @@ struct ForceArith<float> {
 constexpr float kMaskQ = 2.0f * (1.0f + 1e-5f);
 constexpr int kChunk = TFSPH_CHUNK;
 constexpr int kScanChunk = TFSPH_SCAN_CHUNK;
+constexpr int kWideChunk = 8;        // the same in the crowded runs of the fused 1D step
 constexpr int kWalk = TFSPH_WALK;
 // records past the end of a sorted pos / frc array that may be read
 constexpr int kPad = kChunk > kScanChunk ? kChunk : kScanChunk;
@@ -223,6 +224,7 @@ struct Sorted {
     int *src;            // nullable [n]: index in the unsorted arrays of sorted particle dst
     unsigned long long *nmask;   // nullable [rows][n]: neighbour bits per window row (gas)
     R *rec;              // nullable (1D): records on their way into cell ranges (line.hpp)
+    int *runs;           // nullable (1D gas): first cells of the fused step's runs (line.hpp)
 };
 
 struct Flags {

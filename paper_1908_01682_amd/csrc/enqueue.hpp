@@ -68,12 +68,21 @@ inline tfsph_status enqueue_scan(int ncell, Sorted<R> &Sg, Sorted<R> &Sd, int *p
     return TFSPH_OK;
 }
 
-// One fused 1D step (line.hpp) in runs of cpb cells (0: line_cells()).  claimed: the previous step claimed this one's slots;
+// Runs and LDS of the fused 1D step (line.hpp); LDS 0 where the step takes the separate launches.
+template <typename R>
+inline size_t line_step_lds(const Geom<R> &G, int ng, int nd, bool mass_d, int &n_runs)
+{
+    const int cells = line_cells(G.win[0], double(ng) / G.ncell);
+    n_runs = (G.ncell + cells - 1) / cells;
+    return line_lds<R>(ng, nd, G.ncell, G.win[0], n_runs, n_runs, mass_d);
+}
+
+// One fused 1D step in n_runs runs and lds bytes (line_step_lds()).  claimed: the previous step claimed this one's slots;
 // claim: so does this step for the next one.
 template <typename R>
 inline tfsph_status enqueue_line(int ng, int nd, const Geom<R> &G, const Phys<R> &Ph, const Phase<R> &Pg,
-                                 const Phase<R> &Pd, Sorted<R> &Sg, Sorted<R> &Sd, int *partial, const Flags &F, int cpb,
-                                 bool claimed, bool claim, hipStream_t st)
+                                 const Phase<R> &Pd, Sorted<R> &Sg, Sorted<R> &Sd, int *partial, const Flags &F, int n_runs,
+                                 size_t lds, bool claimed, bool claim, hipStream_t st)
 {
     tfsph_status r = TFSPH_OK;
     if (!claimed) r = enqueue_count<R>(ng, nd, G.ncell, Pg, Pd, Sg, Sd, F, st);
@@ -82,19 +91,15 @@ inline tfsph_status enqueue_line(int ng, int nd, const Geom<R> &G, const Phys<R>
     const int bg = blocks_for(ng), bd = blocks_for(nd);
     if (bg + bd > 0) {
         hipLaunchKernelGGL(k_line_scatter<R>, dim3(bg + bd), dim3(kBlock), 0, st, G, Pg, Sg, Pd, Sd, bg,
-                           scan_keeps_counts(G.ncell) ? 1 : 0);
+                           scan_keeps_counts(G.ncell) ? 1 : 0, n_runs);
         LAUNCH_CHECK("line_scatter");
     }
-    const double per_gas = double(ng) / G.ncell, per_dust = double(nd) / G.ncell;
-    if (cpb == 0) cpb = line_cells(G.win[0], per_gas);
-    const int nblocks = (G.ncell + cpb - 1) / cpb;
-    const size_t lds = line_lds<R>(cpb, G.win[0], per_gas, per_dust, Sd.has_mass != 0, nblocks);
     if (Sg.has_mass)
-        hipLaunchKernelGGL((k_line_step<R, kForceIsoMass>), dim3(nblocks), dim3(kBlock), lds, st, G, Ph, Sg, Sd, Pg, Pd,
-                           F, cpb, nblocks, lds, claim ? 1 : 0);
+        hipLaunchKernelGGL((k_line_step<R, kForceIsoMass>), dim3(n_runs), dim3(kBlock), lds, st, G, Ph, Sg, Sd, Pg, Pd,
+                           F, n_runs, lds, claim ? 1 : 0);
     else
-        hipLaunchKernelGGL((k_line_step<R, kForceIsoUniform>), dim3(nblocks), dim3(kBlock), lds, st, G, Ph, Sg, Sd, Pg,
-                           Pd, F, cpb, nblocks, lds, claim ? 1 : 0);
+        hipLaunchKernelGGL((k_line_step<R, kForceIsoUniform>), dim3(n_runs), dim3(kBlock), lds, st, G, Ph, Sg, Sd, Pg,
+                           Pd, F, n_runs, lds, claim ? 1 : 0);
     LAUNCH_CHECK("line_step");
     return TFSPH_OK;
 }

@@ -106,6 +106,7 @@ Sorted<R> carve_phase(Carver &cv, int n, int dim, int ncell, PhaseFlags f)
     S.tmp_idx = cv.take<int>(n);
     S.tmp_id = cv.take<int>(n);
     S.rec = f.line ? cv.take<R>(size_t(n) * (f.mass ? 4 : 2)) : nullptr;
+    S.runs = f.line && f.prs ? cv.take<int>(size_t(ncell) + 2) : nullptr;
     S.nmask = f.mask_rows > 0 ? cv.take<unsigned long long>(size_t(f.mask_rows) * n) : nullptr;
     return S;
 }

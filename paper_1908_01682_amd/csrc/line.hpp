@@ -10,15 +10,18 @@
 // cells and W halo cells, the force and predictor of its own cells, their drag
 // solve, and writes the moved particles: 76 bytes a particle, and the halo of 8
 // cells costs 6% of a run of 128.  The neighbour loops read LDS.  us a step,
-// separate -> fused, FP32: 5000 + 5000 particles 29.0 -> 22.3, 1e6 + 1e6 114 -> 72;
-// 256 uneven waves (5.4M particles, flattened batch) 294 -> 184.
+// separate -> fused, FP32: 5000 + 5000 particles 29 -> 21, 1e6 + 1e6 114 -> 77;
+// 256 uneven waves (5.4M particles, flattened batch) 292 -> 182.
 //
 // Everything is computed by the device functions of the separate launches on a
 // local copy of the grid (cells renumbered, neighbour order kept), so results
-// are bitwise theirs.  A run whose particles do not fit the LDS of the launch
-// works in the global workspace instead; runs share halo particles there, and
+// are bitwise theirs.  Runs are cut by particles (line_cut()).  A run whose particles
+// do not fit the LDS of the launch, or that holds a crowded cell, works in the global
+// workspace instead, with wider loops; runs share halo particles there, and
 // write equal values for them.
 #pragma once
+
+#include <algorithm>
 
 #include "binning.hpp"
 #include "sph.hpp"
@@ -60,9 +63,45 @@ __device__ __forceinline__ R4<R> line_record(const Phase<R> &P, const Sorted<R> 
     return mk4<R>(q.x, q.y, P.m_uniform, R(0));
 }
 
+// The runs of cells of the workgroups: run k of n_runs holds the cells runs[k] .. runs[k + 1] - 1.
+// They are cut by particles, so that crowded cells do not make one workgroup's serial work
+// of a share of the problem: key(c) counts the gas before cell c three times (two neighbour
+// loops), the dust once and the cells line_cell_weight() times (which bounds the cells of a
+// run), width is the average key of a run, and cell c belongs to run (key(c) + key(c + 1)) / 2
+// / width: a cell of more than two widths has a run to itself, and the runs that it spans
+// are empty.  us a step, runs of equal cells -> these (separate launches), 1e5 + 1e5
+// particles, 2 of a phase per cell: even 27 -> 29 (38); 90% of the dust in a tenth of the box 71 ->
+// 41 (55); 90% of both 330 -> 75 (97); 95% in a fiftieth 4889 -> 285 (310); 5000 dust particles
+// in a cell 7298 -> 439 (550); 300 gas particles in a cell 273 -> 225 (202), 1000 1361 -> 765 (620): the
+// neighbour loops of a cell stay one workgroup's, which is the limit of this form.
+__host__ __device__ inline unsigned line_cell_weight(int ng, int nd, int ncell)
+{
+    const unsigned w = (3u * unsigned(ng) + unsigned(nd)) / 4u / unsigned(ncell);
+    return w < 1u ? 1u : w;
+}
+
+__host__ __device__ inline unsigned line_run_width(int ng, int nd, int ncell, int n_runs)
+{
+    return (3u * unsigned(ng) + unsigned(nd) + line_cell_weight(ng, nd, ncell) * unsigned(ncell)) / unsigned(n_runs) + 1u;
+}
+
+// the runs that start at the cells first, first + stride, ... (one past the last cell included)
+template <typename R>
+__device__ __forceinline__ void line_cut(const Geom<R> &G, const Sorted<R> &Sg, const Sorted<R> &Sd, int n_runs, int first,
+                                         int stride)
+{
+    const unsigned w = line_cell_weight(Sg.n, Sd.n, G.ncell), width = line_run_width(Sg.n, Sd.n, G.ncell, n_runs);
+    auto key = [&](int c) { return 3u * unsigned(Sg.start[c]) + unsigned(Sd.start[c]) + w * unsigned(c); };
+    auto run_of = [&](int c) { return int((key(c) + key(c + 1)) / 2u / width); };
+    for (int c = first; c <= G.ncell; c += stride) {
+        const int last = c < G.ncell ? run_of(c) : n_runs;
+        for (int k = c > 0 ? run_of(c - 1) + 1 : 0; k <= last; ++k) Sg.runs[k] = c;
+    }
+}
+
 template <typename R>
 __global__ void __launch_bounds__(kBlock)
-k_line_scatter(Geom<R> G, Phase<R> Pg, Sorted<R> Sg, Phase<R> Pd, Sorted<R> Sd, int blocks_g, int clear)
+k_line_scatter(Geom<R> G, Phase<R> Pg, Sorted<R> Sg, Phase<R> Pd, Sorted<R> Sd, int blocks_g, int clear, int n_runs)
 {
     clear_counts(clear ? Sg.count : nullptr, Sd.count, G.ncell);
     const bool gas = int(blockIdx.x) < blocks_g;
@@ -72,6 +111,7 @@ k_line_scatter(Geom<R> G, Phase<R> Pg, Sorted<R> Sg, Phase<R> Pd, Sorted<R> Sd, 
     } else {
         if (i < Sd.n) line_scatter_one(G, Pd, Sd, i);
     }
+    line_cut(G, Sg, Sd, n_runs, blockIdx.x * kBlock + threadIdx.x, gridDim.x * kBlock);
 }
 
 // LDS of a run of `own` cells with ng gas particles (halo included) and nd dust
@@ -119,20 +159,63 @@ __host__ __device__ inline size_t line_carve(unsigned char *base, int own, int h
     return off;
 }
 
-// Rank of slot k by id in its cell range [b, e) and the record's place there.
-__device__ __forceinline__ int line_rank(const int *ids, int k, int b, int e)
-{
-    const int id = ids[k];
-    int dst = b;
-    for (int j = b; j < e; ++j) dst += ids[j] < id ? 1 : 0;
-    return dst;
-}
-
 // first sorted index of cell u, for u up to one period outside the box of nc cells
 template <typename R>
 __device__ __forceinline__ int line_first(const Sorted<R> &S, int nc, int u)
 {
     return u < 0 ? S.start[u + nc] - S.n : (u >= nc ? S.start[u - nc] + S.n : S.start[u]);
+}
+
+// The dust of a crowded cell c to its sorted places, by the whole workgroup: ids into kBlock
+// equal ranges of their values, then ranks inside a range, so that the ranks of n particles
+// take about n^2 / 256 comparisons (5000 in a cell: a step of 3.67 ms -> 0.43).  lds: kBucketInts.  Uses
+// the cell's range of slot and tmp_idx.
+constexpr int kBucketCell = 512;         // more particles than this go through ranges
+constexpr int kBucketInts = 2 * kBlock + kBlock / 64 + 2;
+template <typename R>
+__device__ __forceinline__ void line_place_buckets(const Phase<R> &P, const Sorted<R> &S, int c, int *lds, unsigned int *flags)
+{
+    int *begin = lds, *at = lds + kBlock, *range = at + kBlock, *waves = range + 2;
+    const int tid = threadIdx.x, b = S.start[c], e = S.start[c + 1];
+    __syncthreads();                     // the last cell's lists are done with
+    if (tid == 0) {
+        range[0] = 0x7fffffff;
+        range[1] = -0x7fffffff - 1;
+    }
+    begin[tid] = 0;
+    __syncthreads();
+    int lo = 0x7fffffff, hi = -0x7fffffff - 1;
+    for (int k = b + tid; k < e; k += kBlock) {
+        lo = min(lo, S.tmp_id[k]);
+        hi = max(hi, S.tmp_id[k]);
+    }
+    atomicMin(&range[0], lo);
+    atomicMax(&range[1], hi);
+    __syncthreads();
+    const unsigned first = range[0], width = (unsigned(range[1]) - first) / kBlock + 1;
+    auto bucket = [&](int id) { return int((unsigned(id) - first) / width); };
+    for (int k = b + tid; k < e; k += kBlock) atomicAdd(&begin[bucket(S.tmp_id[k])], 1);
+    __syncthreads();
+    int total;
+    const int ex = block_exclusive_scan(begin[tid], waves, total);
+    begin[tid] = at[tid] = b + ex;
+    __syncthreads();
+    for (int k = b + tid; k < e; k += kBlock) {
+        const int id = S.tmp_id[k];
+        const int p = atomicAdd(&at[bucket(id)], 1);
+        S.slot[p] = id;
+        S.tmp_idx[p] = k;
+    }
+    __syncthreads();
+    for (int p = b + tid; p < e; p += kBlock) {
+        const int id = S.slot[p], j = bucket(id);
+        const R4<R> q = line_record(P, S, S.tmp_idx[p]);
+        const int dst = rank_in_cell(S.slot, begin[j], at[j], id, p, flags);
+        S.id[dst] = id;
+        S.cell[dst] = c;
+        S.pos[dst] = mk4<R>(q.x, R(0), R(0), q.z);
+        S.vel[0][dst] = q.y;
+    }
 }
 
 // The run of cells [c0, c1) of a workgroup.
@@ -154,7 +237,18 @@ __device__ __forceinline__ void line_run(const Geom<R> &G, const Phys<R> &Ph, co
     Sorted<R> Lg{}, Ld{};
     CellSolve<R> *cs;
     R *off_d, *m_d;
-    const bool local = line_carve<R>(smem, own, H, ng, nd, Sd.has_mass != 0, Lg, Ld, off_d, m_d, cs) <= lds_bytes;
+    __shared__ int s_long;               // a cell that the loops of the global workspace serve better
+    bool local = line_carve<R>(smem, own, H, ng, nd, Sd.has_mass != 0, Lg, Ld, off_d, m_d, cs) <= lds_bytes;
+    if (local && (nd > kBucketCell || ng > 2 * kBlock)) {
+        if (tid == 0) s_long = 0;
+        __syncthreads();
+        for (int c = tid - H; c < own + H; c += kBlock) {
+            const bool gas = first_of(c0 + c + 1) - first_of(c0 + c) > kBlock;
+            if (gas || (c >= 0 && c < own && Sd.start[c0 + c + 1] - Sd.start[c0 + c] > kBucketCell)) s_long = 1;
+        }
+        __syncthreads();
+        local = s_long == 0;
+    }
 
     if (local) {
         Geom<R> Gl = G;
@@ -178,7 +272,7 @@ __device__ __forceinline__ void line_run(const Geom<R> &G, const Phys<R> &Ph, co
         for (int l = tid; l < ng; l += kBlock) {
             const R4<R> q = l == tid ? qg : line_record(Pg, Sg, slot_of(l));
             const int c = Lg.cell[l];
-            const int dst = line_rank(Lg.tmp_id, l, Lg.start[c], Lg.start[c + 1]);
+            const int dst = rank_in_cell(Lg.tmp_id, Lg.start[c], Lg.start[c + 1], Lg.tmp_id[l], l, F.word);
             Lg.id[dst] = Lg.tmp_id[l];
             Lg.pos[dst] = mk4<R>(q.x, R(0), R(0), q.z);
             Lg.vel[0][dst] = q.y;
@@ -186,7 +280,7 @@ __device__ __forceinline__ void line_run(const Geom<R> &G, const Phys<R> &Ph, co
         for (int l = tid; l < nd; l += kBlock) {
             const R4<R> q = l == tid ? qd : line_record(Pd, Sd, da + l);
             const int c = Ld.cell[l];
-            const int dst = line_rank(Ld.tmp_id, l, Ld.start[c], Ld.start[c + 1]);
+            const int dst = rank_in_cell(Ld.tmp_id, Ld.start[c], Ld.start[c + 1], Ld.tmp_id[l], l, F.word);
             Ld.id[dst] = Ld.tmp_id[l];
             off_d[dst] = q.x;
             if (m_d) m_d[dst] = q.z;
@@ -272,11 +366,8 @@ __device__ __forceinline__ void line_run(const Geom<R> &G, const Phys<R> &Ph, co
             return lo;
         };
         auto place = [&](const Phase<R> &P, const Sorted<R> &S, int k, int c) {
-            const int b = S.start[c], e = S.start[c + 1];
             const R4<R> q = line_record(P, S, k);
-            int dst = k;
-            if (e - b <= kMaxRankCell) dst = line_rank(S.tmp_id, k, b, e);
-            else atomicOr(F.word, 8u);
+            const int dst = rank_in_cell<kWideChunk>(S.tmp_id, S.start[c], S.start[c + 1], S.tmp_id[k], k, F.word);
             S.id[dst] = S.tmp_id[k];
             S.cell[dst] = c;
             S.pos[dst] = mk4<R>(q.x, R(0), R(0), q.z);
@@ -286,7 +377,16 @@ __device__ __forceinline__ void line_run(const Geom<R> &G, const Phys<R> &Ph, co
             const int u = c0 - H + cell_of(lsg, nl, l);
             place(Pg, Sg, slot_of(l), u < 0 ? u + nc : (u >= nc ? u - nc : u));
         }
-        for (int l = tid; l < nd; l += kBlock) place(Pd, Sd, da + l, c0 + cell_of(lsd, own, l));
+        auto by_buckets = [&](int c) {
+            const int n_c = lsd[c + 1] - lsd[c];
+            return n_c > kBucketCell && n_c <= kMaxRankCell;
+        };
+        for (int l = tid; l < nd; l += kBlock) {
+            const int c = cell_of(lsd, own, l);
+            if (!by_buckets(c)) place(Pd, Sd, da + l, c0 + c);
+        }
+        for (int c = 0; c < own; ++c)
+            if (by_buckets(c)) line_place_buckets(Pd, Sd, c0 + c, lsd + own + 1, F.word);
         __syncthreads();
         // (the records after a range may belong to a run that has not placed them yet: not read)
         for (int l = lsg[W] + tid; l < lsg[nl - W]; l += kBlock) density_store<R, 1, false>(G, Ph, T, slot_of(l), 1);
@@ -312,6 +412,15 @@ __device__ __forceinline__ void line_run(const Geom<R> &G, const Phys<R> &Ph, co
     }
 }
 
+// The cells [c0, c1) of a run; none of a problem without particles, whose runs are not cut.
+template <typename R>
+__device__ __forceinline__ void line_cells_of(const Sorted<R> &Sg, const Sorted<R> &Sd, int run, int &c0, int &c1)
+{
+    const bool cut = Sg.n + Sd.n > 0;
+    c0 = cut ? Sg.runs[run] : 0;
+    c1 = cut ? Sg.runs[run + 1] : 0;
+}
+
 template <typename R, int KIND>
 __device__ __forceinline__ void line_block(const Geom<R> &G, const Phys<R> &Ph, const Sorted<R> &Sg, const Sorted<R> &Sd,
                                            const Phase<R> &Pg, const Phase<R> &Pd, const Flags &F, int c0, int c1,
@@ -321,7 +430,8 @@ __device__ __forceinline__ void line_block(const Geom<R> &G, const Phys<R> &Ph, 
     if (threadIdx.x == 0) { s_bad = 0; s_one = 0; }
     int bad = 0, one = 0;
     R s2 = signal_floor(Ph);
-    line_run<R, KIND>(G, Ph, Sg, Sd, Pg, Pd, F, c0, c1, lds_bytes, claim, smem, bad, one, s2);
+    if (c0 < c1)
+        line_run<R, KIND>(G, Ph, Sg, Sd, Pg, Pd, F, c0, c1, lds_bytes, claim, smem, bad, one, s2);
     publish_speed(Ph, F, s2);
     if (bad) atomicOr(&s_bad, 1);
     if (one) atomicAdd(&s_one, one);
@@ -337,13 +447,13 @@ __device__ __forceinline__ void line_block(const Geom<R> &G, const Phys<R> &Ph, 
 
 template <typename R, int KIND>
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(R) == 4 ? kLineWaves : 4)))
-k_line_step(Geom<R> G, Phys<R> Ph, Sorted<R> Sg, Sorted<R> Sd, Phase<R> Pg, Phase<R> Pd, Flags F, int cells_per_block,
-            int nblocks, size_t lds_bytes, int claim)
+k_line_step(Geom<R> G, Phys<R> Ph, Sorted<R> Sg, Sorted<R> Sd, Phase<R> Pg, Phase<R> Pd, Flags F, int n_runs,
+            size_t lds_bytes, int claim)
 {
-    extern __shared__ unsigned char smem_raw[];
-    const int c0 = xcd_block(nblocks) * cells_per_block;
-    const int c1 = min(c0 + cells_per_block, G.ncell);
-    line_block<R, KIND>(G, Ph, Sg, Sd, Pg, Pd, F, c0, c1, lds_bytes, claim != 0, smem_raw);
+    extern __shared__ __align__(16) unsigned char smem_line[];     // 16-byte records from the first byte on
+    int c0, c1;
+    line_cells_of(Sg, Sd, xcd_block(n_runs), c0, c1);
+    line_block<R, KIND>(G, Ph, Sg, Sd, Pg, Pd, F, c0, c1, lds_bytes, claim != 0, smem_line);
 }
 
 // Cells of a run: with its halo one gas particle a thread on average, so no phase
@@ -355,21 +465,39 @@ inline int line_cells(int win, double per_gas)
     return cells < 16 ? 16 : (cells > 256 ? 256 : cells);
 }
 
-// LDS of the launch for runs of `cells` cells with `per_gas` and `per_dust` particles
-// a cell on average: 1.6 times that (as fast as 1.35 times: registers allow five
-// workgroups per CU anyway), and three times where runs have a CU to themselves.
+// Gas particles a cell, on average, up to which the fused step is taken: the halo of a run is
+// 4 W cells whatever they hold, so where cells hold many, most of its densities are computed
+// twice.  us a step, fused / separate, FP32 1e5 + 1e5 particles: 4 a cell 33 / 44, with 90% of
+// both phases in a tenth of the box 112 / 148; 10 a cell 43 / 58 and 343 / 284; 20 a cell 103 /
+// 87 and 1216 / 550.  FP64 launches of more than one round of workgroups hold less: 1e6 + 1e6
+// particles, 2 a cell 122 / 144 and 535 / 508, 4 a cell 145 / 170 and 1099 / 690.
+constexpr double kLineGasPerCell = 4.0, kLineGasPerCellMany = 2.5;
+
+// LDS of a launch of all_runs runs, some of them of a problem of ng + nd particles cut in n_runs:
+// what lets all of them be resident at once, where that is at least 1.6 times an average run's
+// need, otherwise 1.6 times it (as fast as 1.35 times; twice: 1e6 + 1e6 particles 79 -> 86 us a
+// step).  0 where the step takes the separate launches: crowded averages, and problems whose
+// keys (line_cut()) do not fit 31 bits.
 template <typename R>
-inline size_t line_lds(int cells, int win, double per_gas, double per_dust, bool mass_d, int nblocks)
+inline size_t line_lds(int64_t ng, int64_t nd, int ncell, int win, int n_runs, int64_t all_runs, bool mass_d)
 {
-    const double room = nblocks > 512 ? 1.6 : 3.0;
-    const int ng = int(per_gas * (cells + 4 * win) * room) + 16, nd = int(per_dust * cells * room) + 16;
+    const double per_gas = double(ng) / ncell, per_dust = double(nd) / ncell, cells = double(ncell) / n_runs;
+    if (3 * ng + nd + 2 * int64_t(ncell) >= int64_t(1) << 30) return 0;
+    const double g = per_gas * (cells + 4 * win) * 1.6 + 16, d = per_dust * cells * 1.6 + 16;
+    if (g + d > 1e5) return 0;
     Sorted<R> Lg{}, Ld{};
     CellSolve<R> *cs;
     R *off_d, *m_d;
-    const size_t most = size_t(nblocks > 512 ? 64 : 144) * 1024;
-    const size_t least = (sizeof(CellSolve<R>) + 2 * sizeof(int)) * cells + 4 * win * sizeof(int) + 64;
-    const size_t lds = line_carve<R>(nullptr, cells, 2 * win, ng, nd, mass_d, Lg, Ld, off_d, m_d, cs);
-    return lds < least ? least : (lds > most ? (most > least ? most : least) : lds);
+    const size_t need = line_carve<R>(nullptr, int(cells) + 1, 2 * win, int(g), int(d), mass_d, Lg, Ld, off_d, m_d, cs);
+    // the lists of the longest run, for one that works in global memory
+    const size_t own = line_run_width((int)ng, (int)nd, ncell, n_runs) / line_cell_weight((int)ng, (int)nd, ncell) + 2;
+    const size_t least = (sizeof(CellSolve<R>) + 2 * sizeof(int)) * own + (4 * win + kBucketInts) * sizeof(int) + 64;
+    const int64_t per_cu = (all_runs + 255) / 256;
+    // (allocated in steps of 1280 bytes; the static variables take a few of the last one)
+    const size_t room = per_cu <= 5 ? size_t(128 / per_cu) * 1280 - 64 : 0;
+    if (per_gas > (sizeof(R) == 8 && room == 0 ? kLineGasPerCellMany : kLineGasPerCell)) return 0;
+    const size_t lds = std::max(std::max(need, least), room);
+    return lds > 144 * 1024 ? (std::max(need, least) > 144 * 1024 ? 0 : 144 * 1024) : lds;
 }
 
 }  // namespace tfsph

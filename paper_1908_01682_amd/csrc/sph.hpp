@@ -16,24 +16,29 @@
 
 namespace tfsph {
 
-// Load the chunk of kScanChunk records starting at b of a range ending at b1.
-// Padded arrays (sorted pos / frc in global memory, kPad spare records at
-// the end) are read straight past b1 from one address; otherwise (LDS) the
+// Records loaded together: kScanChunk from padded arrays, kWideChunk with clamped indices
+// (crowded runs of the fused 1D step, few waves of long ranges: load latency bounds them).
+template <bool Padded>
+constexpr int scan_chunk() { return Padded ? kScanChunk : kWideChunk; }
+
+// Load the chunk of scan_chunk() records starting at b of a range ending at b1.
+// Padded arrays (sorted pos / frc, kPad spare records at
+// the end) are read straight past b1 from one address; otherwise the
 // indices are clamped to the range.
 template <bool Padded, typename V>
-__device__ __forceinline__ void load_chunk(const V *__restrict__ data, int b, int b1, V q[kScanChunk])
+__device__ __forceinline__ void load_chunk(const V *__restrict__ data, int b, int b1, V q[scan_chunk<Padded>()])
 {
-    if (Padded) {
+    if (Padded || b + scan_chunk<Padded>() <= b1) {
         const V *p = data + b;
 #pragma unroll
-        for (int k = 0; k < kScanChunk; ++k) q[k] = p[k];
+        for (int k = 0; k < scan_chunk<Padded>(); ++k) q[k] = p[k];
     } else {
 #pragma unroll
-        for (int k = 0; k < kScanChunk; ++k) q[k] = data[min(b + k, b1 - 1)];
+        for (int k = 0; k < scan_chunk<Padded>(); ++k) q[k] = data[min(b + k, b1 - 1)];
     }
 }
 
-// Visit candidates [b0, b1) of one cell: records are loaded kScanChunk at a time
+// Visit candidates [b0, b1) of one cell: records are loaded scan_chunk() at a time
 // so one memory wait serves several candidates; fn(b, q, rx, ry, rz, valid)
 // gets the record, r = x_a - x_b and whether b is a real candidate (false
 // past b1 in the last chunk; such records are finite but belong elsewhere).
@@ -41,12 +46,13 @@ template <typename R, int DIM, bool Padded = true, typename T = R, typename Fn>
 __device__ __forceinline__ void visit_range(int b0, int b1, const R4<R> *__restrict__ data, T rx0, T ry0, T rz0,
                                             Fn &fn)
 {
-    for (int b = b0; b < b1; b += kScanChunk) {
-        R4<R> q[kScanChunk];
+    constexpr int C = scan_chunk<Padded>();
+    for (int b = b0; b < b1; b += C) {
+        R4<R> q[C];
         load_chunk<Padded>(data, b, b1, q);
         const int rem = b1 - b;        // >= 1: candidate k of the chunk is real when k < rem
 #pragma unroll
-        for (int k = 0; k < kScanChunk; ++k) {
+        for (int k = 0; k < C; ++k) {
             const T rx = rx0 - T(q[k].x);
             const T ry = DIM > 1 ? ry0 - T(q[k].y) : T(0);
             const T rz = DIM > 2 ? rz0 - T(q[k].z) : T(0);

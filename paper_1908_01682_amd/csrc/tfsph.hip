@@ -229,7 +229,6 @@ struct tfsph_ctx {
     size_t ws_bytes;
     hipStream_t last_stream;
     int cells_per_block;
-    bool cells_set = false;     // cells_per_block was chosen by the caller
 };
 
 // record one event of a (start, stop) pair for kernel kind k when profiling
@@ -357,9 +356,11 @@ tfsph_status enqueue_step(tfsph_ctx *c, tfsph_state *s, hipStream_t st, bool fol
     if (c->variant != TFSPH_VARIANT_AUTO) Sg.nmask = nullptr;    // scan the whole window in both passes
     if constexpr (DIM == 1) {
         // timed steps keep the separate launches, whose kinds the timers tell apart
-        if (Sg.rec && Sd.rec && c->variant == TFSPH_VARIANT_AUTO && !c->profiling)
-            return enqueue_line<R>(c->ng, c->nd, G, Ph, Pg, Pd, Sg, Sd, partial, F,
-                                   c->cells_set ? c->cells_per_block : 0, follows, more, st);
+        int n_runs = 0;
+        const size_t lds = Sg.rec && Sd.rec && c->variant == TFSPH_VARIANT_AUTO && !c->profiling
+                               ? line_step_lds(G, c->ng, c->nd, Sd.has_mass != 0, n_runs) : 0;
+        if (lds > 0)
+            return enqueue_line<R>(c->ng, c->nd, G, Ph, Pg, Pd, Sg, Sd, partial, F, n_runs, lds, follows, more, st);
     }
     MARK(TFSPH_KERNEL_BIN);
     tfsph_status r = enqueue_bin<R>(c->ng, c->nd, G, Pg, Pd, Sg, Sd, partial, F, st);
@@ -873,7 +874,6 @@ extern "C" tfsph_status tfsph_set_cells_per_block(tfsph_ctx *c, int32_t cells)
     if (cells < 1 || cells > kMaxCellsPerBlock)
         return fail(TFSPH_E_INVALID_ARG, "cells per block %d outside [1, %d]", cells, kMaxCellsPerBlock);
     c->cells_per_block = cells;
-    c->cells_set = true;
     drop_graph(c->sg);
     return TFSPH_OK;
 }
