@@ -69,11 +69,16 @@ inline tfsph_status enqueue_scan(int ncell, Sorted<R> &Sg, Sorted<R> &Sd, int *p
 }
 
 // Runs and LDS of the fused 1D step (line.hpp); LDS 0 where the step takes the separate launches.
+// Those serve problems of fewer than kLineLeast particles a phase: all of them may crowd in a few
+// cells, whose neighbour loops are one workgroup's in a run (1500 of 1500 in one cell: 1480 us a
+// step fused, 538 separate; even 20 / 28).
+constexpr int kLineLeast = 2048;
 template <typename R>
 inline size_t line_step_lds(const Geom<R> &G, int ng, int nd, bool mass_d, int &n_runs)
 {
     const int cells = line_cells(G.win[0], double(ng) / G.ncell);
     n_runs = (G.ncell + cells - 1) / cells;
+    if (ng < kLineLeast && nd < kLineLeast) return 0;
     return line_lds<R>(ng, nd, G.ncell, G.win[0], n_runs, n_runs, mass_d);
 }
 

@@ -195,6 +195,13 @@ Phase<R> make_phase(const tfsph_phase &ph, int dim)
 // 34.2, 28^2 37.8 / 35.5.  1D waves stay below both lines (10 a particle): FP32 200 5.8 /
 // 30.5, 1500 16.4 / 31.1; FP64 200 7.3 / 30.2.
 constexpr double kSmallPairsF32 = 40000.0, kSmallPairsF64 = 24000.0;
+// That number is of an even state.  Crowded particles have up to n candidates each, one CU's
+// work here and n / 256 workgroups' in the general step, so a phase also holds at most 768
+// particles (three waves per SIMD).  us a step, one workgroup / general: 90% of both phases in a tenth
+// of the box, 1D wave FP32 768 39.6 / 55.4, 1500 70.9 / 59.1, FP64 768 54.9 / 61.0, 1500 168 / 65;
+// all in one cell FP32 640 258 / 234, 768 310 / 270, 832 391 / 300, 1500 1103 / 536, shock 768 498 /
+// 460, 1200 1437 / 749.  Even states lose 10-19 us a step between 768 and 2048 particles.
+constexpr int kSmallParticles = 768;
 constexpr int kSmallSteps = 4096;        // steps per launch
 
 // Dynamic LDS of the one-workgroup step for this problem, 0 when it does not take

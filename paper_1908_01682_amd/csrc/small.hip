@@ -56,14 +56,14 @@ auto with_types(const tfsph_params *p, bool gas_mass, Fn &&f)
 size_t tfsph_host::small_step_lds(const tfsph_params *p, const tfsph_state *s)
 {
     if (p->scheme != TFSPH_SCHEME_IDIC || p->dim > 2) return 0;
-    const int64_t ng = s->gas.n, nd = s->dust.n, most = kSmallOwn * kSmallBlock;
+    const int64_t ng = s->gas.n, nd = s->dust.n, most = kSmallParticles;
     if (ng > most || nd > most || ng + nd == 0) return 0;
     const int rows = mask_rows_of(p);
     if (p->dim == 2 && rows == 0) return 0;
     double cand = double(ng) / ncell_of(p);          // window candidates of a particle
     for (int d = 0; d < p->dim; ++d) cand *= 2 * window_of(p, d) + 1;
     if (double(ng) * cand > (p->precision == TFSPH_F64 ? kSmallPairsF64 : kSmallPairsF32)) return 0;
-    if (ncell_of(p) > 16 * most) return 0;
+    if (ncell_of(p) > 16 * kSmallOwn * kSmallBlock) return 0;
     const size_t lds = with_types(p, s->gas.mass != nullptr, [&](auto r, auto dim, auto kind) {
         return carve_bytes<decltype(r), decltype(dim)::value, decltype(kind)::value>((int)ng, (int)nd, ncell_of(p), rows);
     });
