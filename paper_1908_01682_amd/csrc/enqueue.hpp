@@ -141,7 +141,7 @@ inline tfsph_status enqueue_density(const Geom<R> &G, const Phys<R> &Ph, const S
 {
     if (S.n == 0) return TFSPH_OK;
     if constexpr (DIM == 3) {
-        if (variant == TFSPH_VARIANT_AUTO && tile_density(G, S.n)) {
+        if (variant == TFSPH_VARIANT_AUTO && tile_density(G, S.n, want_frc && S.nmask)) {
             hipLaunchKernelGGL((k_density_tiles<R>), dim3(blocks_for(S.n)), dim3(kBlock), 0, st, G, Ph, S, want_frc);
             LAUNCH_CHECK("density_tiles");
             return TFSPH_OK;

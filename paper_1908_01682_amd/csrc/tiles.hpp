@@ -21,7 +21,7 @@
 // rounding of the half-precision coordinates, so every pair inside the support
 // is kept, and the exact term, evaluated by walk_bits() for the kept ones in
 // the scan's own order, is zero for the few others.  The sums are those of the
-// scan bit for bit.  128^3 box after 100 steps, scan -> tiles: density 352 -> 331 us
+// scan bit for bit.  128^3 box after 100 steps, scan -> tiles: gas density 352 -> 333 us
 // (FP32), MK gas drag 807 -> 613, MK dust drag 639 -> 483; FP64 64^3 step 215 -> 186.
 // VALU issue still bounds all of them: about 190 instructions a row (36 of the test
 // itself per 64 candidates, 64 sign bits) and 39 per visited neighbour.  Coordinates are relative to the middle of the wave's run
@@ -32,10 +32,11 @@
 
 namespace tfsph {
 
-// Widest run of cells (along x) of the targets that share one origin: 16 cells
-// keep |x| below 9 cells, half-precision steps of 2^-8.  Wider spread targets
-// form further groups.
 constexpr int kTileWaves = 4;        // waves per SIMD of the FP32 kernels
+// Widest run of cells (along x) of the targets that share one origin: 16 cells
+// keep |x| within 9 cells, of at most 2 units each (tile_windows()): 18, where a
+// half-precision step is 2^-6.  The inclusion radius grows with it (tile_groups()).
+// Wider spread targets form further groups.
 constexpr int kTileSpan = 15;
 constexpr int kTileGroups = 3;       // groups of targets per wave; any left over scan their windows
 constexpr int kTileRun = 512;        // longest candidate run of a group and row
@@ -354,15 +355,21 @@ inline bool tile_windows(const Geom<R> &G, int n)
     return true;
 }
 
-// Whether the density pass of n particles takes the tile kernel.  Its FP32 form holds 4
-// waves per SIMD against 7 of the scan: with 4097 to 7168 waves (1024 SIMDs) it takes
-// two rounds where the scan takes one.  IDIC step, us, tiles / scan: 72^3 particles
-// (5832 waves) 184 / 178; 64^3 (4096) 134 / 135; 80^3 (8000) 223 / 241.
+// Whether the density pass of n particles takes the tile kernel (masks: it records them).
+// The FP32 form holds 4 waves per SIMD against 7 of the scan: up to 7 per SIMD the scan runs in
+// one round, and the tile kernel is at best as fast.  Without masks (dust) the scan saves their
+// stores and loses to the tiles only while the dust is even.  us a launch, tiles / scan,
+// box of n^3 particles fresh and after 100 steps, gas: 32^3 30.3 / 27.1 and 33.2 / 33.7; 45^3
+// 49.8 / 45.7, 40.7 / 41.9; 64^3 53.4 / 54.2, 53.5 / 52.7; 72^3 74.7 / 73.0, 80.5 / 71.1; 80^3 (8000
+// waves) 93.6 / 117, 96.7 / 107; 96^3 146 / 162, 150 / 153; 128^3 318 / 361, 333 / 352.  Dust: 64^3
+// 49.3 / 48.7, 59.6 / 48.3; 96^3 140 / 151, 184 / 152; 128^3 298 / 330, 402 / 352.  FP64 holds few
+// waves either way: 32^3 33 / 38 and 37 / 49, 64^3 77 / 113 and 83 / 121, dust 75 / 96 and 96 / 113.
+constexpr int kScanWaves = 7 * 4 * 256;      // 7 per SIMD of 256 CUs
 template <typename R>
-inline bool tile_density(const Geom<R> &G, int n)
+inline bool tile_density(const Geom<R> &G, int n, bool masks)
 {
     const int waves = n / 64 + (n % 64 != 0);
-    return tile_windows(G, n) && !(sizeof(R) == 4 && waves > 4 * 1024 && waves <= 7 * 1024);
+    return tile_windows(G, n) && (sizeof(R) == 8 || (masks && waves > kScanWaves));
 }
 
 }  // namespace tfsph
