@@ -41,6 +41,15 @@ def _problem(cells, n_gas, n_dust, width, seed, clump=0, rough=False):
     return I.Problem("tiles", p, phase(n_gas), phase(n_dust), 1)
 
 
+CASES = {
+    "wide_cells": dict(cells=(9, 7, 6), n_gas=3400, n_dust=3400, width=3.99, rough=True),
+    "wide_long_rows": dict(cells=(41, 5, 4), n_gas=7400, n_dust=5000, width=3.99, rough=True),
+    "mid_long_rows": dict(cells=(37, 4, 5), n_gas=6700, n_dust=6000, width=3.0, rough=True),
+    "at_the_line": dict(cells=(6, 5, 5), n_gas=1375, n_dust=1300, width=2.0),
+    "crowded_cell": dict(cells=(10, 9, 8), n_gas=1500, n_dust=1200, width=2.0, clump=600),
+}
+
+
 def _dispatches(prob, n):
     p = prob.params
     D = p.cell_width()
@@ -62,6 +71,17 @@ def _compare(prob, precision, scheme, steps):
         got.append((_bits(sim, scheme), sim.flags()))
         sim.close()
     assert got[0] == got[1]
+
+
+@pytest.mark.parametrize("scheme", [0, 1, 2, 3])
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("name", sorted(CASES))
+def test_cases_that_take_tiles_equal_window_scans_bitwise(name, precision, scheme):
+    prob = _problem(seed=len(name), **CASES[name])
+    assert _dispatches(prob, max(prob.gas.n, prob.dust.n))
+    prob.params = prob.params.replace(scheme=scheme)
+    banner(f"tiles dispatch {name} precision {precision} scheme {scheme}")
+    _compare(prob, precision, scheme, 2)
 
 
 @pytest.mark.parametrize("name,cells,n,width", [
