@@ -504,48 +504,31 @@ __device__ __forceinline__ void sub_prod(A &s, T f, T x)
         s -= A(f * x);
 }
 
-// Distance of a pair and its inverse from r^2 in the term type T of an R state.
-// FP64 terms start from a hardware estimate (the FP32 reciprocal square root of
-// an FP32 state, relative error 1e-7; v_rsq_f64 of an FP64 state) and take one
-// Newton step (1e-14), for the FP64 state a third-order one and a correction of r by
-// its residual, which leaves less than an ulp (the library's FP64 square root and
-// division together are three times the instructions): against 80-bit arithmetic over
-// 2^-30 < r^2 < 4 the rms error of 1/r is 5.3e-17 (1.0 / sqrt(r^2): 6.7e-17), of r 4.7e-17
-// (both).  r^2 = 0 (the pair of a particle with itself) gives r = 0 or nearly so and a
-// finite inverse, whose terms vanish because f'(0) = 0; a candidate that is not valid gets
-// an inverse of exactly 0.  The walk took 68 instructions per neighbour in 3D before, 57
-// with it: 128^3 box step 801 -> 784 us, FP64 64^3 step 186 -> 172, 1D shock step 53.6 -> 52.3.
-template <typename R, typename T>
-__device__ __forceinline__ void pair_distance(T r2, bool ok, T &r, T &ir)
+// Distance of a pair and its inverse from r^2, for FP64 terms: r and 1/r correctly rounded, as the IEEE
+// square root and division give them, in half their instructions (no scaling of the exponent, one
+// estimate for both).  The hardware's estimate of 1/sqrt(r^2) goes through a coupled Newton step for
+// the root and half its inverse (Goldschmidt), then either result is corrected twice by its
+// residual from a fused multiply-add.  A candidate that is not valid, and the pair of a particle with
+// itself (r^2 = 0), get 0 for both.  Residuals of r^2 below 1e-290 underflow (1e-15 relative).
+// us a step, IEEE -> this, FP64 64^3 box 183 -> 175, 1D shock 55 -> 54.
+__device__ __forceinline__ void pair_distance(double r2, bool ok, double &r, double &ir)
 {
-    if constexpr (!std::is_same<T, double>::value) {
-        r = fsqrt(r2);
-        ir = (ok && r2 > T(0)) ? frcp(r) : T(0);
-    } else if constexpr (std::is_same<R, float>::value) {
-        const double y0 = double(ok ? frsq(fmaxf(float(r2), 1e-36f)) : 0.0f);
-        const double e = __builtin_fma(-(r2 * y0), y0, 1.0);
-        ir = __builtin_fma(0.5 * y0, e, y0);
-        r = r2 * ir;
-    } else {
-        const double s2 = fmax(r2, 1e-280);
-        const double y0 = ok ? __builtin_amdgcn_rsq(s2) : 0.0;
-        const double e = __builtin_fma(-(s2 * y0), y0, 1.0);
-        ir = __builtin_fma(y0 * e, __builtin_fma(0.375, e, 0.5), y0);
-        const double r0 = s2 * ir;
-        r = __builtin_fma(0.5 * ir, __builtin_fma(-r0, r0, s2), r0);
-    }
+    const double y = ok && !(r2 <= 0.0) ? __builtin_amdgcn_rsq(r2) : 0.0;
+    const double g0 = r2 * y, h0 = 0.5 * y;
+    const double e0 = __builtin_fma(-h0, g0, 0.5);
+    const double h = __builtin_fma(h0, e0, h0);
+    const double g1 = __builtin_fma(g0, e0, g0);
+    const double g2 = __builtin_fma(__builtin_fma(-g1, g1, r2), h, g1);
+    r = __builtin_fma(__builtin_fma(-g2, g2, r2), h, g2);
+    const double i0 = h + h;
+    const double i1 = __builtin_fma(__builtin_fma(-r, i0, 1.0), i0, i0);
+    ir = __builtin_fma(__builtin_fma(-r, i1, 1.0), i1, i1);
 }
 
-// 1 / x in the term type: FP64 terms of an FP32 state from the FP32 reciprocal and one Newton step
-template <typename R, typename T>
-__device__ __forceinline__ T pair_rcp(T x)
+__device__ __forceinline__ void pair_distance(float r2, bool ok, float &r, float &ir)
 {
-    if constexpr (std::is_same<T, double>::value && std::is_same<R, float>::value) {
-        const double y0 = double(frcp(float(x)));
-        return __builtin_fma(y0, __builtin_fma(-x, y0, 1.0), y0);
-    } else {
-        return frcp(x);
-    }
+    r = fsqrt(r2);
+    ir = (ok && r2 > 0.0f) ? frcp(r) : 0.0f;
 }
 
 template <typename R, int DIM, int KIND, bool PADDED = true>
@@ -574,42 +557,53 @@ __device__ __forceinline__ void gas_force_at(const Geom<R> &G, const Phys<R> &Ph
         else
             for_window<R, DIM, SS, PADDED>(G, cx, cy, cz, oa, S.start, S.frc, fn);
     };
-    // f'(q) = 3 (t1^2 - s^2) with t1 = sat(1 - r / h), s = sat(1 - r / 2h); the factor 3 (and
-    // a uniform mass) multiplies the sums
-    const T mh1 = -inv_h, mh2 = T(-0.5) * inv_h;
-    auto df3 = [&](T r) {
-        const T sv = sat(T(1) + mh2 * r);
-        const T t1 = sat(T(1) + mh1 * r);
-        return t1 * t1 - sv * sv;
-    };
-    // In 1D an FP32 state of a wave of amplitude 1e-4 lives from differences of 1e-7 of a term, where
-    // the last bit of an FP64 term decides roundings of the state: that loop scales every term by
-    // itself, as the sums have always been formed.
-    constexpr bool scaled = !(DIM == 1 && KIND != kForceGeneral && std::is_same<R, float>::value);
-    if constexpr (!scaled) {
+    // The isothermal loops of an FP32 state in 2D and 3D leave the factors 3 (of f'), a uniform mass and
+    // the kernel's norm to the end: 57 instructions per neighbour in 3D instead of 68 (128^3 box step
+    // 801 -> 784 us), and the FP64 sums round to the same FP32 results.  In 1D an FP32 state of a wave of
+    // amplitude 1e-4 lives from differences of 1e-7 of a term, where the last bit of an FP64 term decides
+    // roundings of the state, and an FP64 state shows every bit: those loops, and the general one, scale
+    // every term by itself, as the sums have always been formed.
+    constexpr bool scaled = DIM > 1 && KIND != kForceGeneral && std::is_same<R, float>::value;
+    if constexpr (scaled) {
+        const T mh1 = -inv_h, mh2 = T(-0.5) * inv_h;
         visit([&](int b, T Pb, T rx, T ry, T rz, bool ok) {
             const T r2 = rx * rx + ry * ry + rz * rz;
             T r, ir;
             if constexpr (std::is_same<T, double>::value) {
+                // 1/r from the hardware FP32 reciprocal square root and one Newton step in FP64 (relative
+                // error about 1e-14); r^2 = 0 (the self pair) gives r = 0 and a finite inverse, whose
+                // term vanishes because f'(0) = 0
+                const double y0 = double(ok ? frsq(fmaxf(float(r2), 1.17549435e-38f)) : 0.0f);
+                const double e = __builtin_fma(-(r2 * y0), y0, 1.0);
+                ir = __builtin_fma(0.5 * y0, e, y0);
+                r = r2 * ir;
+            } else {
+                pair_distance(r2, ok, r, ir);
+            }
+            // f'(q) = 3 (t1^2 - s^2) with t1 = sat(1 - r / h), s = sat(1 - r / 2h)
+            const T sv = sat(T(1) + mh2 * r);
+            const T t1 = sat(T(1) + mh1 * r);
+            T fac = (Pa + Pb) * (t1 * t1 - sv * sv) * ir;
+            if constexpr (KIND == kForceIsoMass) fac *= T(pos[b].w);
+            sub_prod(ax, fac, rx);
+            sub_prod(ay, fac, ry);
+            sub_prod(az, fac, rz);
+        });
+    } else if constexpr (KIND != kForceGeneral) {
+        visit([&](int b, T Pb, T rx, T ry, T rz, bool ok) {
+            const T r2 = rx * rx + ry * ry + rz * rz;
+            T r, ir;
+            if constexpr (std::is_same<T, double>::value && std::is_same<R, float>::value) {
                 const double y0 = double(frsq(float(r2)));
                 const double y = y0 * (1.5 - 0.5 * r2 * (y0 * y0));
                 const bool live = ok && r2 > 0.0;
                 ir = live ? y : 0.0;              // self pair and padding contribute 0
                 r = live ? r2 * y : 0.0;
             } else {
-                pair_distance<R, T>(r2, ok, r, ir);
+                pair_distance(r2, ok, r, ir);
             }
             const T mb = KIND == kForceIsoMass ? T(pos[b].w) : mu_m;
             const T fac = mb * (Pa + Pb) * spline_df(r * inv_h) * ir;
-            sub_prod(ax, fac, rx);
-        });
-    } else if constexpr (KIND != kForceGeneral) {
-        visit([&](int b, T Pb, T rx, T ry, T rz, bool ok) {
-            const T r2 = rx * rx + ry * ry + rz * rz;
-            T r, ir;
-            pair_distance<R, T>(r2, ok, r, ir);
-            T fac = (Pa + Pb) * df3(r) * ir;
-            if constexpr (KIND == kForceIsoMass) fac *= T(pos[b].w);
             sub_prod(ax, fac, rx);
             sub_prod(ay, fac, ry);
             sub_prod(az, fac, rz);
@@ -622,20 +616,21 @@ __device__ __forceinline__ void gas_force_at(const Geom<R> &G, const Phys<R> &Ph
         visit([&](int b, T Pb, T rx, T ry, T rz, bool ok) {
             const T r2 = rx * rx + ry * ry + rz * rz;
             T r, ir;
-            pair_distance<R, T>(r2, ok, r, ir);
-            if (ok && r * inv_h < T(2) && r2 > T(0)) {
-                const T gfac = df3(r) * ir;               // grad_a W = 3 gfac * gnorm * r_vec
+            pair_distance(r2, ok, r, ir);
+            const T qq = r * inv_h;
+            if (ok && qq < T(2) && r2 > T(0)) {
+                const T gfac = spline_df(qq) * ir;        // grad_a W = gfac * gnorm * r_vec
                 const T vx = va[0] - T(S.vel[0][b]);
                 const T vy = DIM > 1 ? va[1] - T(S.vel[1][b]) : T(0);
                 const T vz = DIM > 2 ? va[2] - T(S.vel[2][b]) : T(0);
                 const T vr = vx * rx + vy * ry + vz * rz;
                 T Pi = T(0);
                 if (Ph.av && vr < T(0)) {
-                    const T mu = T(Ph.h) * vr * pair_rcp<R, T>(r2 + T(Ph.eta2));
+                    const T mu = T(Ph.h) * vr / (r2 + T(Ph.eta2));
                     const T cb = sound_of(Ph, S.energy ? S.energy[b] : R(0));
                     const T cbar = T(0.5) * (ca + cb);
                     const T rbar = T(0.5) * (rhoa + T(S.rho[b]));
-                    Pi = (-T(Ph.av_alpha) * cbar * mu + T(Ph.av_beta) * mu * mu) * pair_rcp<R, T>(rbar);
+                    Pi = (-T(Ph.av_alpha) * cbar * mu + T(Ph.av_beta) * mu * mu) / rbar;
                 }
                 const T mb = per_mass ? T(pos[b].w) : mu_m;
                 const T fac = mb * (Pa + Pb + Pi) * gfac;
