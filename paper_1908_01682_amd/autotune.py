@@ -7,11 +7,13 @@ size distribution) it times every candidate on the real batch.
 
 Plain step (``tune_plain``): the candidates are the cells owned by one block of the
 update kernel (cell sums, 2x2 solve, particle update), for a problem signature (device
-name, dim, precision, particle and cell counts).
+name, dim, precision, particle and cell counts, scheme, equation of state, viscosity,
+neighbour window).  Small problems that run in one workgroup and 1D problems of the fused
+step have no update kernel: their steps do not depend on the choice.
 
 Both check that every candidate leaves a bitwise-identical state (the method's sums are
 evaluated in a fixed order, so the launch shape must not change a single bit) and cache
-the fastest in a JSON file.
+the fastest in a JSON file, under keys that hold the revision of the kernels it was timed on.
 
 Cache path: $TFSPH_AUTOTUNE_CACHE, else ~/.cache/tfsph/autotune.json.
 """
@@ -19,6 +21,7 @@ from __future__ import annotations
 
 import hashlib
 import json
+import math
 import os
 import time
 from typing import Iterable, Optional
@@ -29,6 +32,8 @@ CANDIDATE_BLOCKS = (256, 512, 768, 1024)
 CANDIDATE_CELLS_PER_BLOCK = (16, 32, 64, 128, 256)
 CANDIDATE_FLAT_CELLS = (64, 128, 256)
 PERSISTENT, FLAT = 0, 1
+# raised when a kernel that the choices are timed on changes: older cached choices are then timed anew
+KERNEL_REVISION = 2
 
 
 def cache_path() -> str:
@@ -37,11 +42,11 @@ def cache_path() -> str:
 
 
 def signature(device_name: str, probs, precision: int) -> str:
-    """Key of a batch: device, dim, precision, instance count and a coarse size histogram."""
+    """Key of a batch: device, dim, precision, instance count, a coarse size histogram and the kernels."""
     ns = np.array([p.gas.n + p.dust.n for p in probs], dtype=np.int64)
     hist = np.histogram(np.log2(np.maximum(ns, 1)), bins=8, range=(0, 32))[0]
     raw = json.dumps(dict(dev=device_name, dim=int(probs[0].params.dim), prec=int(precision), n=int(len(ns)),
-                          hist=hist.tolist(), nmax=int(ns.max())), sort_keys=True)
+                          hist=hist.tolist(), nmax=int(ns.max()), kernels=KERNEL_REVISION), sort_keys=True)
     return hashlib.sha1(raw.encode()).hexdigest()[:16]
 
 
@@ -139,11 +144,15 @@ def tune(bs, steps: int = 20, blocks: Iterable[int] = CANDIDATE_BLOCKS, use_cach
 
 
 def plain_signature(device_name: str, sim) -> str:
-    """Key of a single problem: device, dim, precision, particle and cell counts, scheme."""
+    """Key of a single problem: device, dim, precision, particle and cell counts, scheme, the gas terms
+    (equation of state, viscosity), the neighbour window and the kernels."""
     p = sim.prob.params
+    win = [math.ceil(2.0 * p.h * p.n_cells[d] / (p.hi[d] - p.lo[d]) - 1e-12) for d in range(p.dim)]
     raw = json.dumps(dict(dev=device_name, dim=int(p.dim), prec=int(sim.precision), ng=int(sim.gas.n),
                           nd=int(sim.dust.n), cells=[int(c) for c in p.n_cells[:p.dim]],
-                          scheme=int(getattr(p, "scheme", 0)), kind="plain"), sort_keys=True)
+                          scheme=int(getattr(p, "scheme", 0)), eos=int(p.eos),
+                          viscous=bool(p.av_alpha or p.av_beta), window=win, kernels=KERNEL_REVISION, kind="plain"),
+                     sort_keys=True)
     return hashlib.sha1(raw.encode()).hexdigest()[:16]
 
 
