@@ -43,7 +43,9 @@ WORKLOADS = {
 }
 
 # floating-point operations the method needs, per unit (see the roofline notes in bench output)
-FLOPS_PER_CANDIDATE = 8       # r^2 of a window candidate: 3 sub + 3 mul + 2 add
+FLOPS_PER_CANDIDATE = 8       # r^2 of a window candidate: 3 sub + 3 mul + 2 add.  The scans form it for every
+#                               candidate; behind the matrix-core support test (takes_tiles()) the vector ALU
+#                               forms it for the pairs only
 FLOPS_PER_DENSITY_PAIR = 13   # q = sqrt(r^2)/h (2), f(q) (9), m f accumulated (2)
 FLOPS_PER_FORCE_PAIR = 28     # r^2 (8), r and 1/r (2), q (1), f'(q) (7), m (P_a+P_b) f'/r (4), 3 fma (6)
 
@@ -89,6 +91,27 @@ def support_pairs(prob, phase: str = "gas", other: str = "gas") -> int:
     return int(np.sum(n))
 
 
+SCAN_WAVES = 7 * 4 * 256      # waves of the FP32 density scan that 256 CUs hold at once
+
+
+def takes_tiles(prob, n: int) -> bool:
+    """Whether the pair kernels over n candidates test the support on the matrix cores: 3D windows of
+    one cell, cells of at most 4 h, at most 55 candidates per pair of rows on average."""
+    p = prob.params
+    if p.dim != 3 or 6 * n > 55 * int(np.prod(p.n_cells)):
+        return False
+    D = [(p.hi[d] - p.lo[d]) / p.n_cells[d] for d in range(3)]
+    return all(math.ceil(2.0 * p.h / w - 1e-12) == 1 and w <= 4.0 * p.h for w in D)
+
+
+def density_work(prob, cand: int, pairs: int):
+    """(kernel, vector flops) of the FP32 gas density pass: beyond one round of the scan it takes the
+    matrix-core test."""
+    if takes_tiles(prob, prob.gas.n) and -(-prob.gas.n // 64) > SCAN_WAVES:
+        return "k_density_tiles", (FLOPS_PER_CANDIDATE + FLOPS_PER_DENSITY_PAIR) * pairs
+    return "k_density", FLOPS_PER_CANDIDATE * cand + FLOPS_PER_DENSITY_PAIR * pairs
+
+
 def update_kernel_bytes(prob) -> float:
     """Algorithmic HBM bytes of one launch of the update kernel (cell sums, implicit solve,
     particle update): per particle it must read its position (dim x 4 B) and velocity
@@ -115,7 +138,7 @@ def step_bytes(prob) -> float:
     return float(g.n * gas_b + s.n * dust_b + 32 * int(np.prod(p.n_cells[:d])))
 
 
-COUNTER_SOURCES = ("common.hpp", "sph.hpp", "binning.hpp", "enqueue.hpp", "host.hpp")
+COUNTER_SOURCES = ("common.hpp", "sph.hpp", "binning.hpp", "enqueue.hpp", "host.hpp", "tiles.hpp")
 
 
 def kernel_source_sha() -> str:
@@ -224,7 +247,9 @@ def drag_schemes(prob, I, T, torch, steps=100, warmup=50, cpu_steps=0, counts=No
         counts["cross_pairs"] = support_pairs(prob, "gas", "dust")
     if "gas_pairs" not in counts:
         counts["gas_pairs"] = support_pairs(prob)
-    cand, cross = counts["cross_candidates"], counts["cross_pairs"]
+    cross = counts["cross_pairs"]
+    # distances that the drag sums form on the vector ALU
+    cand = cross if takes_tiles(prob, max(prob.gas.n, prob.dust.n)) else counts["cross_candidates"]
     press = FLOPS_PER_FORCE_PAIR * (counts["gas_pairs"] - prob.gas.n)
     # k_pair_gas and k_pair_dust run back to back inside one timed kind
     work = {
@@ -247,7 +272,7 @@ def drag_schemes(prob, I, T, torch, steps=100, warmup=50, cpu_steps=0, counts=No
         sim.step(steps)
         torch.cuda.synchronize()
         T.tfsph_profile(sim.ctx, False)
-        names = (("binning", "k_density", "k_gas_predict", "k_update") if name == "IDIC" else
+        names = (("binning", density_work(q, 0, 0)[0], "k_gas_predict", "k_update") if name == "IDIC" else
                  ("binning", "k_density_gas_and_dust", "k_gas_predict", "k_pair_gas_and_dust"))
         kms = {}
         for k, kind in zip(names, kinds):
@@ -468,8 +493,9 @@ def main(argv=None):
     T.tfsph_profile(sim.ctx, False)
     kernel_ms = {}
     # per launch of the kind; with the IMEX step the force and update kinds cover the stage kernels
-    names = (("k_density", "k_gas_predict", "k_update", "binning") if not imex_main else
-             ("k_density", "imex_force_stages", "imex_update_stages", "binning"))
+    density = density_work(prob, 0, 0)[0]
+    names = ((density, "k_gas_predict", "k_update", "binning") if not imex_main else
+             (density, "imex_force_stages", "imex_update_stages", "binning"))
     for name, kind in zip(names, (T.TFSPH_KERNEL_DENSITY, T.TFSPH_KERNEL_FORCE, T.TFSPH_KERNEL_UPDATE,
                                   T.TFSPH_KERNEL_BIN)):
         ms, n = T.tfsph_profile_read(sim.ctx, kind)
@@ -493,12 +519,12 @@ def main(argv=None):
     pairs = support_pairs(prob)
     peak_tf = FP32_PEAK_TFLOPS
     work = {
-        "k_density": ("alu", FLOPS_PER_CANDIDATE * cand + FLOPS_PER_DENSITY_PAIR * pairs, peak_tf, "TFLOP/s"),
+        density: ("alu", density_work(prob, cand, pairs)[1], peak_tf, "TFLOP/s"),
         "k_gas_predict": ("alu", FLOPS_PER_FORCE_PAIR * (pairs - prob.gas.n), peak_tf, "TFLOP/s"),
         "k_update": ("hbm", update_kernel_bytes(prob), HBM_PEAK_GBS, "GB/s"),
     }
     if imex_main:   # the density kernel is the same launch; the other kinds mix several stage kernels
-        work = {"k_density": work["k_density"]}
+        work = {density: work[density]}
     per_kernel = {}
     for k, (bound, amount, peak, unit) in work.items():
         t = kernel_ms[k] * 1e-3
