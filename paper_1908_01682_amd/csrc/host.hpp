@@ -77,7 +77,8 @@ struct PhaseFlags {
     bool line = false;   // 1D: records of the fused step (line.hpp)
 };
 
-// 1D problems whose step runs in the fused form when the workspace holds its records
+// 1D problems whose step runs in the fused form when the workspace holds its records and the
+// cells are not crowded on average (line_lds())
 inline bool line_step(const tfsph_params *p)
 {
     return p->dim == 1 && p->scheme == TFSPH_SCHEME_IDIC && window_of(p, 0) <= 2 && p->eos == TFSPH_ISOTHERMAL &&

@@ -23,9 +23,11 @@
 // the scan's own order, is zero for the few others.  The sums are those of the
 // scan bit for bit.  128^3 box after 100 steps, scan -> tiles: gas density 352 -> 333 us
 // (FP32), MK gas drag 807 -> 613, MK dust drag 639 -> 483; FP64 64^3 step 215 -> 186.
-// VALU issue still bounds all of them: about 190 instructions a row (36 of the test
-// itself per 64 candidates, 64 sign bits) and 39 per visited neighbour.  Coordinates are relative to the middle of the wave's run
-// of cells, in units of the support radius 2h.
+// The density pass issues VALU instructions in three quarters of the slots (4490 a wave over the
+// first hundred steps of the box), the drag sums in two thirds; by the listing about 190 a row (36 of
+// the test itself per 64 candidates, 64 sign bits) and 39 per visited neighbour.
+// Coordinates are relative to the middle of the wave's run of cells, in units of the
+// support radius 2h.
 #pragma once
 
 #include "sph.hpp"
