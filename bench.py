@@ -94,11 +94,12 @@ def support_pairs(prob, phase: str = "gas", other: str = "gas") -> int:
 SCAN_WAVES = 7 * 4 * 256      # waves of the FP32 density scan that 256 CUs hold at once
 
 
-def takes_tiles(prob, n: int) -> bool:
-    """Whether the pair kernels over n candidates test the support on the matrix cores: 3D windows of
-    one cell, cells of at most 4 h, at most 55 candidates per pair of rows on average."""
+def takes_tiles(prob, least: int, most: int) -> bool:
+    """Whether the FP32 pair kernels between phases of least and most particles test the support on the
+    matrix cores: 3D windows of one cell, cells of at most 4 h, 38 to 55 candidates per pair of rows on average."""
     p = prob.params
-    if p.dim != 3 or 6 * n > 55 * int(np.prod(p.n_cells)):
+    cells = int(np.prod(p.n_cells))
+    if p.dim != 3 or 6 * most > 55 * cells or 6 * least < 38 * cells:
         return False
     D = [(p.hi[d] - p.lo[d]) / p.n_cells[d] for d in range(3)]
     return all(math.ceil(2.0 * p.h / w - 1e-12) == 1 and w <= 4.0 * p.h for w in D)
@@ -107,7 +108,7 @@ def takes_tiles(prob, n: int) -> bool:
 def density_work(prob, cand: int, pairs: int):
     """(kernel, vector flops) of the FP32 gas density pass: beyond one round of the scan it takes the
     matrix-core test."""
-    if takes_tiles(prob, prob.gas.n) and -(-prob.gas.n // 64) > SCAN_WAVES:
+    if takes_tiles(prob, prob.gas.n, prob.gas.n) and -(-prob.gas.n // 64) > SCAN_WAVES:
         return "k_density_tiles", (FLOPS_PER_CANDIDATE + FLOPS_PER_DENSITY_PAIR) * pairs
     return "k_density", FLOPS_PER_CANDIDATE * cand + FLOPS_PER_DENSITY_PAIR * pairs
 
@@ -249,7 +250,7 @@ def drag_schemes(prob, I, T, torch, steps=100, warmup=50, cpu_steps=0, counts=No
         counts["gas_pairs"] = support_pairs(prob)
     cross = counts["cross_pairs"]
     # distances that the drag sums form on the vector ALU
-    cand = cross if takes_tiles(prob, max(prob.gas.n, prob.dust.n)) else counts["cross_candidates"]
+    cand = cross if takes_tiles(prob, *sorted((prob.gas.n, prob.dust.n))) else counts["cross_candidates"]
     press = FLOPS_PER_FORCE_PAIR * (counts["gas_pairs"] - prob.gas.n)
     # k_pair_gas and k_pair_dust run back to back inside one timed kind
     work = {

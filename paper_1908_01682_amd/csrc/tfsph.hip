@@ -589,7 +589,7 @@ tfsph_status enqueue_step_pair(tfsph_ctx *c, tfsph_state *s, hipStream_t st)
     };
     bool tiles = false;
     if constexpr (DIM == 3) {
-        tiles = c->variant == TFSPH_VARIANT_AUTO && tile_windows(G, std::max(c->ng, c->nd));
+        tiles = c->variant == TFSPH_VARIANT_AUTO && tile_windows(G, std::min(c->ng, c->nd), std::max(c->ng, c->nd));
         if (tiles) drag(IntC<1>{});
     }
     if (!tiles) drag(IntC<0>{});

@@ -341,17 +341,22 @@ k_density_tiles(Geom<R> G, Phys<R> Ph, Sorted<R> S, int want_frc)
     density_finish<R>(G, Ph, S, a, me, acc * G.wnorm, want_frc);
 }
 
-// Whether the n candidates of a 3D problem take the tile path: a window of one cell
-// per axis, cells at most four smoothing lengths wide (coarser ones would widen the
-// rounding bound, and scans of such windows are rare), and on average at most 55
-// candidates per pair of rows (6 cells): near kMaskBits = 64 many pairs are visited
-// whole and the test is wasted.  IDIC step, us, tiles / scan: 2.2^3 particles per cell
-// (64 per pair) 138.5 / 131.1, 2.1^3 (56) 114.4 / 113.5 (MK 238 / 259), 2.05^3 (51)
-// 104.7 / 110.8.
+// Whether 3D pair sums between a phase of `least` and one of `most` particles take the tile path: a
+// window of one cell per axis, cells at most four smoothing lengths wide (coarser ones would
+// widen the rounding bound, and scans of such windows are rare), and on average at most 55
+// candidates per pair of rows (6 cells): near kMaskBits = 64 many pairs are visited whole
+// and the test is wasted.  IDIC step, us, tiles / scan: 2.2^3 particles per cell (64 per pair) 138.5 /
+// 131.1, 2.1^3 (56) 114.4 / 113.5 (MK 238 / 259), 2.05^3 (51) 104.7 / 110.8.  Few candidates leave the
+// matrices empty: at least 38 per pair in FP32, 25 in FP64.  Tiles / scan by particles per cell, MK step
+// 80^3 FP32: 1 385 / 219, 3 434 / 376, 5 482 / 474, 6 504 / 523, 7 529 / 570; IDIC 100^3 FP32: 5 346 / 338, 6 350 /
+// 346, 7 365 / 378; MK 32^3 FP64: 3 185 / 162, 4 184 / 181, 5 189 / 194; IDIC 64^3 FP64: 1 164 / 139, 3 160 / 172.
+constexpr double kTilePairMost = 55.0;
 template <typename R>
-inline bool tile_windows(const Geom<R> &G, int n)
+constexpr double tile_pair_least() { return sizeof(R) == 4 ? 38.0 : 25.0; }
+template <typename R>
+inline bool tile_windows(const Geom<R> &G, int least, int most)
 {
-    if (G.dim != 3 || 6.0 * n > 55.0 * G.ncell) return false;
+    if (G.dim != 3 || 6.0 * most > kTilePairMost * G.ncell || 6.0 * least < tile_pair_least<R>() * G.ncell) return false;
     for (int d = 0; d < 3; ++d)
         if (G.win[d] != 1 || G.delta[d] > R(4) * G.h) return false;
     return true;
@@ -371,7 +376,7 @@ template <typename R>
 inline bool tile_density(const Geom<R> &G, int n, bool masks)
 {
     const int waves = n / 64 + (n % 64 != 0);
-    return tile_windows(G, n) && (sizeof(R) == 8 || (masks && waves > kScanWaves));
+    return tile_windows(G, n, n) && (sizeof(R) == 8 || (masks && waves > kScanWaves));
 }
 
 }  // namespace tfsph

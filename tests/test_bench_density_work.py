@@ -17,11 +17,15 @@ def test_density_kernel_and_its_vector_flops():
     assert bench.density_work(_box(64 ** 3, 32), 1000, 100) == ("k_density", 8 * 1000 + 13 * 100)
     assert bench.density_work(_box(one_round, 40), 1, 1)[0] == "k_density"
     assert bench.density_work(_box(one_round + 1, 40), 1, 1)[0] == "k_density_tiles"
-    # two cells of window, cells beyond 4 h, crowded pairs of rows, one and two dimensions
-    assert not bench.takes_tiles(_box(1, 64, h=1.0 / 64), 1)
-    assert not bench.takes_tiles(_box(1, 64, h=1.0 / 260), 1)
-    assert bench.takes_tiles(_box(1, 6), 55 * 36) and not bench.takes_tiles(_box(1, 6), 55 * 36 + 1)
-    assert not bench.takes_tiles(I.wave_2d(n_side=16), 10)
+    # two cells of window, cells beyond 4 h, crowded and sparse pairs of rows, one and two dimensions
+    ok = dict(least=8 * 64 ** 3, most=8 * 64 ** 3)
+    assert bench.takes_tiles(_box(1, 64), **ok)
+    assert not bench.takes_tiles(_box(1, 64, h=1.0 / 64), **ok)
+    assert not bench.takes_tiles(_box(1, 64, h=1.0 / 260), **ok)
+    assert bench.takes_tiles(_box(1, 6), 38 * 36, 55 * 36)
+    assert not bench.takes_tiles(_box(1, 6), 38 * 36, 55 * 36 + 1)
+    assert not bench.takes_tiles(_box(1, 6), 38 * 36 - 1, 55 * 36)
+    assert not bench.takes_tiles(I.wave_2d(n_side=16), 2048, 2048)
 
 
 def test_counters_belong_to_the_tile_kernel_too():

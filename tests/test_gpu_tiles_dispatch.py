@@ -1,9 +1,11 @@
 """The matrix-core support test where it is really taken: cases that assert the dispatch conditions of the
-kernels they aim at (a window of one cell, cells below four smoothing lengths, at most 55 candidates
-per pair of rows on average; the FP32 density pass also more waves than one round of the scan holds),
+kernels they aim at (a window of one cell, cells below four smoothing lengths, 38 (FP64: 25) to 55
+candidates per pair of rows on average; the FP32 density pass also more waves than one round of the scan holds),
 with cells up to the width that widens the inclusion radius most, rows longer than a group of 16
-cells, populations on either side of the line and a sparse grid with a crowded cell.  Bitwise the
-window scans."""
+cells, populations on either side of the lines and a grid with a crowded cell.  Bitwise the window
+scans, and sparse grids in their time."""
+import time
+
 import numpy as np
 import pytest
 
@@ -43,17 +45,18 @@ def _problem(cells, n_gas, n_dust, width, seed, clump=0, rough=False):
 
 CASES = {
     "wide_cells": dict(cells=(9, 7, 6), n_gas=3400, n_dust=3400, width=3.99, rough=True),
-    "wide_long_rows": dict(cells=(41, 5, 4), n_gas=7400, n_dust=5000, width=3.99, rough=True),
+    "wide_long_rows": dict(cells=(41, 5, 4), n_gas=7400, n_dust=5200, width=3.99, rough=True),
     "mid_long_rows": dict(cells=(37, 4, 5), n_gas=6700, n_dust=6000, width=3.0, rough=True),
     "at_the_line": dict(cells=(6, 5, 5), n_gas=1375, n_dust=1300, width=2.0),
-    "crowded_cell": dict(cells=(10, 9, 8), n_gas=1500, n_dust=1200, width=2.0, clump=600),
+    "crowded_cell": dict(cells=(10, 9, 8), n_gas=5200, n_dust=4700, width=2.0, clump=600),
 }
 
 
-def _dispatches(prob, n):
+def _dispatches(prob, *ns, pairs=38):
     p = prob.params
     D = p.cell_width()
-    return 6 * n <= 55 * int(np.prod(p.n_cells)) and all(2.0 * p.h <= d * (1 + 1e-12) <= 4.0 * p.h for d in D)
+    cells = int(np.prod(p.n_cells))
+    return 6 * max(ns) <= 55 * cells and 6 * min(ns) >= pairs * cells and all(2.0 * p.h <= d * (1 + 1e-12) <= 4.0 * p.h for d in D)
 
 
 def _bits(sim, scheme):
@@ -78,7 +81,7 @@ def _compare(prob, precision, scheme, steps):
 @pytest.mark.parametrize("name", sorted(CASES))
 def test_cases_that_take_tiles_equal_window_scans_bitwise(name, precision, scheme):
     prob = _problem(seed=len(name), **CASES[name])
-    assert _dispatches(prob, max(prob.gas.n, prob.dust.n))
+    assert _dispatches(prob, prob.gas.n, prob.dust.n)
     prob.params = prob.params.replace(scheme=scheme)
     banner(f"tiles dispatch {name} precision {precision} scheme {scheme}")
     _compare(prob, precision, scheme, 2)
@@ -109,6 +112,46 @@ def test_fp32_density_passes_that_scan(n, dust):
     prob.params = prob.params.replace(scheme=2)
     banner(f"tiles dispatch scan n {n} dust {dust}")
     _compare(prob, 0, 2, 1)
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+def test_grids_below_the_line_equal_window_scans_bitwise(precision):
+    """A phase at the line, and one particle short of it."""
+    pairs = (38, 25)[precision]
+    for n in (pairs * 150 // 6, pairs * 150 // 6 - 1):
+        prob = _problem((6, 5, 5), n + 60, n, 2.0, 13)
+        assert _dispatches(prob, n + 60, n, pairs=pairs) == (n == pairs * 25)
+        prob.params = prob.params.replace(scheme=2)
+        banner(f"tiles dispatch line {n} precision {precision}")
+        _compare(prob, precision, 2, 2)
+
+
+def _best(step, n=8):
+    step(2)
+    torch.cuda.synchronize()
+    best = float("inf")
+    for _ in range(4):
+        t = time.perf_counter()
+        step(n)
+        torch.cuda.synchronize()
+        best = min(best, time.perf_counter() - t)
+    return best
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("cells", [64, 128])
+def test_sparse_grids_take_the_time_of_window_scans(cells, precision):
+    """64^3 + 64^3 particles, 1 or 1/8 a cell: the drag sums on tiles took 1.4 to 2.2 times the scans' step."""
+    prob = I.dusty_box(n_side=64, cells_per_axis=cells)
+    prob.params = prob.params.replace(scheme=2, t_stop=0.05, h=0.5 / cells, dt=1e-5)
+    banner(f"tiles dispatch sparse {cells} precision {precision}")
+    t = []
+    for variant in (T.TFSPH_VARIANT_AUTO, T.TFSPH_VARIANT_GLOBAL):
+        sim = T.Simulation(prob, precision=precision)
+        T.tfsph_set_kernel_variant(sim.ctx, variant)
+        t.append(_best(sim.step))
+        sim.close()
+    assert t[0] < 1.2 * t[1], t
 
 
 def test_small_fp32_density_passes_cost_no_more_than_scans():
